@@ -26,6 +26,7 @@ namespace ecnt {
 
 constexpr int kColTile = 64;       // columns per wavefront (one lane per column)
 constexpr int kBasisChunk = 32;    // basis vectors per reorthogonalization launch
+constexpr int kCUs = 256;           // compute units of an MI355X
 constexpr int kMaxShifts = 64;
 constexpr int kMaxK = 512;
 constexpr int kBlk = 16;           // probe columns per block of the block-Lanczos form

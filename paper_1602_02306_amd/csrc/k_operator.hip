@@ -533,7 +533,7 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
                                                         int64_t ntiles, const T *__restrict__ X,
                                                         const double *__restrict__ xs_all,
                                                         double c1, double bd1, double bo1, double c2,
-                                                        double bd2, double bo2,
+                                                        double bd2, double bo2, int nzc,
                                                         const T *__restrict__ Z, double cz,
                                                         T *__restrict__ out)
 {
@@ -549,7 +549,8 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
     __shared__ V su[UW * UW * 64];
     __shared__ V stp[TW * TW * 64];
     const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
-    const int cg = (int)(L / ntiles);   // column-group-major
+    const int64_t cgz = L / ntiles;     // column group, then z chunk; tiles fastest
+    const int cg = (int)(cgz / nzc), zc = (int)(cgz % nzc);
     const int64_t tile = L % ntiles;
     const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
     // lanes past the last column load column 0 and store nothing, and take
@@ -559,6 +560,11 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
     const int c0 = colok ? craw : 0;
     const int seg = find_seg(seg_tile, nseg, tile);
     const int d0 = seg_dims[3 * seg], d1 = seg_dims[3 * seg + 1], d2 = seg_dims[3 * seg + 2];
+    // this workgroup's planes [za, zb); an empty chunk leaves as a whole
+    const int zlen = (d2 + nzc - 1) / nzc;
+    const int za = zc * zlen, zb = min(d2, za + zlen);
+    if (za >= zb) return;
+    const int zs0 = za > 0 ? za - 1 : 0;   // t is needed from plane za - 1 on
     const int nty = (d1 + 7) / 8;
     const int lt = (int)(tile - seg_tile[seg]);
     const int bx = (lt / nty) * 8, by = (lt % nty) * 8;   // block origin (inside the grid)
@@ -635,23 +641,25 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
     for (int v = 0; v < VW; ++v) xsc[v] = xs ? (R)xs[c0 + v] : R(1);
     // u of the own lines at z-1, z, z+1 (um, u0, un); ring-2 u at z (r2)
     T um[NT][VW], u0[NT][VW], un[NT][VW], r2[3][VW], tm2[4][VW], tm1[4][VW];
-    const int64_t e1 = d2 > 1 ? zs : 0;
+    const int64_t e0 = (int64_t)zs0 * zs;
+    const int64_t em = zs0 > 0 ? e0 - zs : 0, e1 = zs0 + 1 < d2 ? e0 + zs : 0;
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
-        T a[VW], b[VW];
-        ldT(base + off[q], a);
+        T p[VW], a[VW], b[VW];
+        ldT(base + em + off[q], p);
+        ldT(base + e0 + off[q], a);
         ldT(base + e1 + off[q], b);
 #pragma unroll
         for (int v = 0; v < VW; ++v) {
-            um[q][v] = zero;
+            um[q][v] = (w[q] != 0.0 && zs0 > 0) ? p[v] : zero;
             u0[q][v] = w[q] != 0.0 ? a[v] : zero;
-            un[q][v] = (w[q] != 0.0 && d2 > 1) ? b[v] : zero;
+            un[q][v] = (w[q] != 0.0 && zs0 + 1 < d2) ? b[v] : zero;
         }
     }
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
         T a[VW];
-        ldT(base + off2[s], a);
+        ldT(base + e0 + off2[s], a);
 #pragma unroll
         for (int v = 0; v < VW; ++v) r2[s][v] = w2[s] != 0.0 ? a[v] : zero;
     }
@@ -659,10 +667,12 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int v = 0; v < VW; ++v) tm2[q][v] = tm1[q][v] = zero;
-    for (int z = 0; z <= d2; ++z) {
-        const bool has_t = z < d2, has_n = z + 1 < d2, has_nn = z + 2 < d2;
-        const int64_t enn = has_nn ? (int64_t)(z + 2) * zs : 0;
-        const int64_t en = has_n ? (int64_t)(z + 1) * zs : 0;
+    for (int z = zs0; z <= zb; ++z) {
+        // (z == zb is the last value: nothing is loaded for the one after it)
+        const bool has_t = z < d2, has_n = z + 1 < d2, more = z < zb;
+        const bool ld_n = has_n && more, ld_nn = z + 2 < d2 && more;
+        const int64_t enn = ld_nn ? (int64_t)(z + 2) * zs : 0;
+        const int64_t en = ld_n ? (int64_t)(z + 1) * zs : 0;
         const int64_t ep = z >= 1 ? (int64_t)(z - 1) * zs : 0;
         // loads in flight during this z value: own lines at z+2, ring 2 at z+1, Z at z-1
         T unn[NT][VW], r2n[3][VW], zv[4][VW];
@@ -727,7 +737,7 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
             }
         }
         // out at z-1 on the quadrant (t at z-1 of the neighbours outside it from LDS)
-        if (z >= 1) {
+        if (z > za) {
             const R znt = has_t ? R(1) : R(0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -773,10 +783,10 @@ __global__ __launch_bounds__(1024) void k_quad_sweep_wg(int C, int ncg, int nseg
             for (int q = 0; q < NT; ++q) {
                 um[q][v] = u0[q][v];
                 u0[q][v] = un[q][v];
-                un[q][v] = (w[q] != 0.0 && has_nn) ? unn[q][v] : zero;
+                un[q][v] = (w[q] != 0.0 && ld_nn) ? unn[q][v] : zero;
             }
 #pragma unroll
-            for (int s = 0; s < 3; ++s) r2[s][v] = (w2[s] != 0.0 && has_n) ? r2n[s][v] : zero;
+            for (int s = 0; s < 3; ++s) r2[s][v] = (w2[s] != 0.0 && ld_n) ? r2n[s][v] : zero;
         }
     }
 }
@@ -1211,16 +1221,40 @@ static void quad_sweep_t(const Plan &p, const void *X, const double *xs, double 
                                                     (T *)out);
 }
 
+// z chunks of the workgroup sweep.  A CU holds one workgroup (its planes take
+// 122 KiB of LDS), so a launch takes ceil(workgroups / 256) rounds of the
+// planes that one workgroup walks: its own zlen, two more for t at its ends,
+// and about two for the loads before the first one.  The split with the least
+// product is taken.  Measured, one chunk against this split: 32^3 x 64 columns
+// (16 blocks: 8 chunks) 98 -> 20 us a sweep, 40^3 x 128 (50: 5) 130 -> 47,
+// 37x29x43 x 200 (80: 3) 134 -> 62; 64^3 x 512 (512 blocks) stays whole, where
+// the planes loaded twice would only add.
+static int quad_wg_chunks(const Plan &p, int64_t groups)
+{
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int c = 1; c <= p.max_d2 && c <= 64; ++c) {
+        const int zlen = (p.max_d2 + c - 1) / c;
+        const int64_t t = ((groups * c + kCUs - 1) / kCUs) * (zlen + (c > 1 ? 4 : 2));
+        if (t < cost) {
+            cost = t;
+            best = c;
+        }
+    }
+    return best;
+}
+
 template <typename T, int VW, bool HASZ>
 static void quad_sweep_wg_t(const Plan &p, const void *X, const double *xs, double c1, double bd1,
                             double bo1, double c2, double bd2, double bo2, const void *Z, double cz,
                             void *out, hipStream_t st)
 {
     const int ncg = (p.C + 64 * VW - 1) / (64 * VW);
-    dim3 grid((unsigned)(p.ntiles * ncg));
+    const int nzc = quad_wg_chunks(p, p.ntiles * ncg);
+    dim3 grid((unsigned)(p.ntiles * ncg * nzc));
     k_quad_sweep_wg<T, VW, HASZ><<<grid, 1024, 0, st>>>(p.C, ncg, p.nseg, p.seg_row, p.seg_tile,
                                                         p.seg_dims, p.ntiles, (const T *)X, xs, c1,
-                                                        bd1, bo1, c2, bd2, bo2, (const T *)Z, cz,
+                                                        bd1, bo1, c2, bd2, bo2, nzc, (const T *)Z, cz,
                                                         (T *)out);
 }
 

@@ -406,6 +406,23 @@ def test_fused_quadratic_sweep_matches_two_sweeps(ec, name, tile):
     assert float((a.per_probe - b.per_probe).abs().max()) <= 1e-12 * nu
 
 
+@pytest.mark.parametrize("dims,m", [((8, 8, 1), 3), ((5, 17, 2), 33), ((9, 10, 67), 5), ((16, 9, 33), 32),
+                                    ((24, 24, 64), 64)])
+@pytest.mark.parametrize("vec", ["f64", "f32"])
+def test_fused_quadratic_sweep_z_chunks(ec, dims, m, vec):
+    """The workgroup sweep splits the z range when its line blocks alone leave
+    CUs idle: one to many chunks, ragged last ones, against two plain sweeps.
+    FP64: the rounding of a few steps; FP32: its stated bound."""
+    wl = W.Workload("z", dims, "wells", 3, -8.0, -2.0, "cheb", m, 4)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)
+    a = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, wl.k, vec=vec, val=vec, tune={"tile": "8x8-wg"})
+    b = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, wl.k, vec=vec, val=vec, tune={"tile": "4x4-unfused"})
+    tol = 1e-12 if vec == "f64" else FP32_BOUND
+    assert float((a.per_probe - b.per_probe).abs().max()) <= tol * P.A.n
+    assert float((a.alpha - b.alpha).abs().max()) <= (1e-11 if vec == "f64" else FP32_BOUND) * float(b.alpha.abs().max())
+
+
 # FP32 storage form: A values, probes, Lanczos vectors and basis in FP32;
 # alpha/beta, every dot product and norm and the tridiagonal eigensolve in
 # FP64.  Parity with the FP64 oracle is not expected to 1e-10; the stated
