@@ -19,13 +19,13 @@ namespace ecnt {
 // ------------------------------------------------------------------ profiling
 enum Family { F_CHEB = 0, F_CSR, F_DOTS, F_UPDATE, F_SETUP, F_FIN, F_QUAD, F_BDOTS, F_BUPD,
               F_VGRAD, F_CHEB2, F_LDL, F_LDLE, F_BKDOTS, F_BKUPD, F_BKNORM, F_BKQUAD,
-              F_STA, F_FUSED, F_COUNT };
+              F_STA, F_FUSED, F_SWEEP, F_COUNT };
 static const char *kFamilyName[F_COUNT] = {"op_cheb_sweep", "op_csr", "lz_dots", "lz_update",
                                            "lz_setup", "lz_finalize", "quadrature", "bw_dots",
                                            "bw_update", "bw_vgrad", "op_cheb_quad",
                                            "op_ldl_solve", "op_ldl_elementwise", "blk_dots",
                                            "blk_update", "blk_normalize", "blk_quadrature",
-                                           "op_a_stencil", "lz_fused"};
+                                           "op_a_stencil", "lz_fused", "lz_sweep"};
 static std::mutex g_prof_mu;
 static bool g_prof_on = false;
 static ecnt_kernel_stat g_stats[F_COUNT];
@@ -133,7 +133,12 @@ size_t plan_layout(Plan &p, char *base)
     p.basis = take(slot * (p.k + 1));
     const int ntmp = p.prec_kind == ECNT_PREC_CHEB_LAPLACIAN ? 3 : (p.prec_kind == ECNT_PREC_LDL ? 2 : 0);
     for (int t = 0; t < 3; ++t) p.tmp[t] = t < ntmp ? take(blk) : nullptr;
-    p.part = (double *)take(sizeof(double) * (size_t)p.nchunk * kPartRows * p.wave_cols);
+    p.part = (double *)take(sizeof(double) * (size_t)p.nchunk * p.part_rows * p.wave_cols);
+    if (p.onesweep) {
+        p.ec = (double *)take(sizeof(double) * p.k * NC);
+        p.cu = (double *)take(sizeof(double) * NC);
+        p.cr = (double *)take(sizeof(double) * NC);
+    }
     p.sig = (double *)take(sizeof(double) * (p.k + 1) * NC);
     p.alpha = (double *)take(sizeof(double) * p.k * NC);
     p.beta = (double *)take(sizeof(double) * (p.k + 1) * NC);
@@ -460,6 +465,41 @@ static ecnt_status make_plan(Plan &p, int64_t n, int64_t m, int S, const ecnt_pr
     return ECNT_OK;
 }
 
+// The one-sweep step serves the plain FP64 recurrence (the differentiated form
+// keeps the coefficients of the two-read step, the FP32 form its points of
+// rounding) up to the slots that a workgroup's wavefronts can hold.  Its
+// partial sums take k + 2 rows a chunk, not kPartRows, and it needs k + 2 more
+// doubles per column: where k is large the chunks get longer until it takes no
+// more workspace than the two-read form, which runs where none is long enough.
+// No size was found where the two-read form is faster: whole counts of 33 k to
+// 390 k rows and 64 to 512 columns took 0.62 to 0.80 of its time, and it makes
+// as many launches per step.
+static void plan_onesweep(Plan &p, SegHost &sh)
+{
+    p.onesweep = 0;
+    p.part_rows = kPartRows;
+    if (p.vec_f32 || p.grad || p.arnoldi || p.block || p.k > kSweepMaxK) return;
+    const size_t most = plan_layout(p, nullptr);
+    const int64_t rpc = p.rpc;
+    const std::vector<int64_t> chunk = sh.chunk;
+    p.onesweep = 1;
+    p.part_rows = p.k + 2;
+    while (plan_layout(p, nullptr) > most) {
+        if (p.rpc >= p.n) {   // as short as it gets
+            p.onesweep = 0;
+            p.part_rows = kPartRows;
+            p.rpc = rpc;
+            sh.chunk = chunk;
+            p.nchunk = (int)sh.chunk[p.nseg];
+            return;
+        }
+        p.rpc += (p.rpc + 15) / 16;
+        for (int b = 0; b < p.nseg; ++b)
+            sh.chunk[b + 1] = sh.chunk[b] + (sh.row[b + 1] - sh.row[b] + p.rpc - 1) / p.rpc;
+        p.nchunk = (int)sh.chunk[p.nseg];
+    }
+}
+
 // Segment tables: nseg problems of ns[b] rows (grids dims[3b..3b+2], d2
 // contiguous) and shifts taus[b*S..]; then geometry and workspace size.
 static ecnt_status set_segments(Plan &p, SegHost &sh, int nseg, const int64_t *ns,
@@ -495,6 +535,7 @@ static ecnt_status set_segments(Plan &p, SegHost &sh, int nseg, const int64_t *n
         if (ns[b] >= 2) p.st_ref_row = sh.row[b];
     col_geometry(p);
     row_geometry(p, sh);
+    plan_onesweep(p, sh);
     plan_layout(p, nullptr);
     return ECNT_OK;
 }
@@ -863,12 +904,35 @@ static void enqueue_wave(const Plan &p, const ecnt_csr *A, const void *probes, h
         Timed t(F_SETUP, blk_b + (double)p.n * p.C * (p.vec_f32 ? 4 : 8) / p.S, st);
         launch_setup(p, probes, st);
     }
+    const size_t slot = slot_bytes(p);
+    char *basis = (char *)p.basis;
+    if (p.onesweep) {
+        void *z = basis + (size_t)p.k * slot;   // slot k receives C u_i
+        for (int i = 0; i < p.k; ++i) {
+            apply_op(p, A, basis + (size_t)i * slot, nullptr, z, i + 1, st);
+            {
+                Timed t(F_DOTS, 2 * blk_b, st);
+                launch_dot_uz(p, i, z, st);
+            }
+            {
+                Timed t(F_FIN, 0.0, st);
+                launch_sweep_fin(p, i, st);
+            }
+            Timed t(F_SWEEP, (i + (i + 1 < p.k ? 4 : 3)) * blk_b, st);
+            launch_sweep(p, i, z, st);
+        }
+        {
+            Timed t(F_FIN, 0.0, st);
+            launch_sweep_fin(p, p.k, st);
+        }
+        Timed t(F_QUAD, 0.0, st);
+        launch_tridiag(p, st);
+        return;
+    }
     {
         Timed t(F_FIN, 0.0, st);
         launch_setup_fin(p, st);
     }
-    const size_t slot = slot_bytes(p);
-    char *basis = (char *)p.basis;
     for (int i = 1; i <= p.k; ++i) {
         void *x = basis + (size_t)(i - 1) * slot;   // slot i-1 holds q_i (unnormalized)
         void *y = basis + (size_t)i * slot;         // slot i receives C q_i

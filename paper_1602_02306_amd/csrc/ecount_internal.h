@@ -29,6 +29,8 @@ constexpr int kBasisChunk = 32;    // basis vectors per reorthogonalization laun
 constexpr int kCUs = 256;           // compute units of an MI355X
 constexpr int kMaxShifts = 64;
 constexpr int kMaxK = 512;
+constexpr int kSweepSlots = 16;    // basis slots per wavefront of the one-sweep Lanczos step
+constexpr int kSweepMaxK = 7 * kSweepSlots;   // seven wavefronts per workgroup
 constexpr int kBlk = 16;           // probe columns per block of the block-Lanczos form
 constexpr int kBlkMaxK = 32;       // block-Lanczos steps (T_k of order <= 512)
 constexpr int kBlkChunk = 32;      // basis blocks per block reorthogonalization launch
@@ -88,7 +90,7 @@ struct Plan {
     void *basis = nullptr;     // (k+1) slots of n * C elements, slot_elems() apart
     size_t slot_pad = 0;       // elements between consecutive slots beyond n * C
     void *tmp[3] = {nullptr, nullptr, nullptr};
-    double *part = nullptr;    // nchunk * kPartRows * C
+    double *part = nullptr;    // nchunk * part_rows * C
     double *sig = nullptr;     // (k+1) * C
     double *alpha = nullptr;   // k * C
     double *beta = nullptr;    // (k+1) * C
@@ -96,7 +98,12 @@ struct Plan {
     double *kappa = nullptr;   // C                 (beta_i * sig_{i-2})
     double *runmax = nullptr;  // C
     double *nu = nullptr;      // C
-
+    // ---- one-sweep Lanczos step (k_sweep.hip) ----
+    int onesweep = 0;
+    int part_rows = 64;        // rows per chunk of the partial sums (kPartRows, or k + 2)
+    double *ec = nullptr;      // k * NC: slot weights of u_{i+1}
+    double *cu = nullptr;      // NC: weight of u_i in u_{i+1}
+    double *cr = nullptr;      // NC: weight of r_i in u_{i+1}
     double *s_out = nullptr;   // Ct  per-column quadrature s_c (wave views are offset)
     double *minabs = nullptr;  // Ct
     double *jac = nullptr;     // S * n (Jacobi scaling)
@@ -207,6 +214,10 @@ void launch_dots(const Plan &p, int step, int l0, int nb, bool gram, hipStream_t
 void launch_dots_fin(const Plan &p, int step, int l0, int nb, bool gram, hipStream_t st);
 void launch_update(const Plan &p, int step, int l0, int nb, bool first, bool last, hipStream_t st);
 void launch_norm_fin(const Plan &p, int step, hipStream_t st);
+// the one-sweep step: u_i . z, the scalars of step i, the sweep (z = C u_i)
+void launch_dot_uz(const Plan &p, int i, const void *z, hipStream_t st);
+void launch_sweep_fin(const Plan &p, int i, hipStream_t st);
+void launch_sweep(const Plan &p, int i, const void *z, hipStream_t st);
 void launch_tridiag(const Plan &p, hipStream_t st);
 // the one-launch Lanczos form of small problems (k_small.hip)
 constexpr int kFusedMaxRows = 3072;   // rows of the largest segment

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void k_setup(int C, int m, int c_off, int nct,
                                                int nseg, const int64_t *__restrict__ seg_row,
                                                const int64_t *__restrict__ seg_chunk,
                                                const T *__restrict__ V, T *__restrict__ slot0,
-                                               double *__restrict__ part)
+                                               int rows, double *__restrict__ part)
 {
     __shared__ double red[4][kColTile];
     const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void k_setup(int C, int m, int c_off, int nct,
     red[wv][lane] = acc;
     __syncthreads();
     if (wv == 0 && c < C)
-        part[(size_t)chunk * kPartRows * C + c] =
+        part[(size_t)chunk * rows * C + c] =
             red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
 }
 
@@ -353,11 +353,11 @@ void launch_setup(const Plan &p, const void *probes, hipStream_t st)
     if (p.vec_f32)
         k_setup<float><<<red_grid(p), 256, 0, st>>>(p.C, p.m, p.c_off, p.nct, p.rpc, p.nseg,
                                                     p.seg_row, p.seg_chunk, (const float *)probes,
-                                                    (float *)p.basis, p.part);
+                                                    (float *)p.basis, p.part_rows, p.part);
     else
         k_setup<double><<<red_grid(p), 256, 0, st>>>(p.C, p.m, p.c_off, p.nct, p.rpc, p.nseg,
                                                      p.seg_row, p.seg_chunk, (const double *)probes,
-                                                     (double *)p.basis, p.part);
+                                                     (double *)p.basis, p.part_rows, p.part);
 }
 
 void launch_setup_fin(const Plan &p, hipStream_t st)

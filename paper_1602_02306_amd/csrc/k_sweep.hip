@@ -1,0 +1,343 @@
+// One-sweep Lanczos step: Algorithm 1 with full reorthogonalization at every
+// step, reading the basis once per step instead of twice (k_lanczos.hip reads
+// it for the dots and again for the update).
+//
+// The reorthogonalization of step i's vector is delayed past the operator: C
+// is applied to the vector u_i that has only been taken through the
+// three-term recurrence, and the sweep that finishes q_i also forms u_{i+1}
+// and its dots with q_0..q_i.  With h = Q^T u_i (from the previous sweep) and
+// z = C u_i, per column (indices from 0, beta_i couples q_{i-1} and q_i):
+//   r      = u_i - Q h,          beta_i = |r|,  q_i = r / beta_i
+//   C r    = z - C Q h = z - h_{i-1} u_i - Q t,    t = T h
+//   alpha^ = r^T C r / beta_i^2
+//   u_{i+1} = C r / beta_i - alpha^ q_i - beta_i q_{i-1}
+// where C Q h follows from the recurrence the basis satisfies (T the Lanczos
+// matrix so far, its last column completed by u_i itself).  h is of the order
+// of rounding (it is what the local recurrence loses in one step), so the
+// second-order terms of C Q h that are dropped lie below rounding, and
+// |r|^2 = |u_i|^2 - |h|^2 loses nothing.  alpha_i = alpha^ + h_i of the next
+// step (the part of u_{i+1} left along q_i).  The basis stays orthogonal as in
+// the two-read form: every q_i has been orthogonalized against all of q_0..
+// q_{i-1} before C q_i enters anything.
+//
+// Bound: HBM.  Step i reads i + 2 block vectors and writes 2, against 2i + 3
+// read and 1 written for dots and update.  64^3 x 512 columns, k = 30: 119 ms
+// (5.0 TB/s) and 11 ms for u.z, against 109 ms of updates (5.2 TB/s) and 81 ms
+// of dots (6.6 TB/s); 32^3 x 64, k = 100: 19.5 ms against 33.1.
+//
+// Slots: 0..k-1 hold r_0.. (unnormalized, scales sig as in k_lanczos.hip);
+// u_i lies in slot i until its sweep overwrites it with r_i; slot k holds z.
+#include <float.h>
+
+#include "device_common.h"
+#include "ecount_internal.h"
+
+namespace ecnt {
+
+// Rows of the partial sums of a chunk: 0 u.u, 1 + l slot_l.u (l < i), i + 1 u.z
+
+// part[chunk][row][c] = sum over the chunk's rows of U * Z
+__global__ __launch_bounds__(256) void k_dot_uz(int C, int nct, int64_t rpc, int nseg,
+                                                const int64_t *__restrict__ seg_row,
+                                                const int64_t *__restrict__ seg_chunk,
+                                                const double *__restrict__ U,
+                                                const double *__restrict__ Z, int rows, int row,
+                                                double *__restrict__ part)
+{
+    __shared__ double red[4][64];
+    const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
+    const int ct = (int)(L % nct);
+    const int64_t chunk = L / nct;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int c = ct * 64 + lane;
+    const int seg = find_seg(seg_chunk, nseg, chunk);
+    const int64_t r0 = seg_row[seg] + (chunk - seg_chunk[seg]) * rpc;
+    const int64_t r1 = min(seg_row[seg + 1], r0 + rpc);
+    double a = 0.0;
+    if (c < C) {
+        for (int64_t r = r0 + wv; r < r1; r += 4) {
+            const size_t e = (size_t)r * C + c;
+            a += U[e] * Z[e];
+        }
+    }
+    red[wv][lane] = a;
+    __syncthreads();
+    if (wv == 0 && c < C)
+        part[((size_t)chunk * rows + row) * C + c] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+// Chunk sums of rows 0..gridDim.y-1, each left in the segment's first chunk.
+__global__ void k_sweep_sum(int C, int nseg, int rows, const int64_t *__restrict__ seg_chunk,
+                            double *__restrict__ part)
+{
+    const int NC = nseg * C;
+    const int vc = blockIdx.x * 64 + (threadIdx.x & 63);
+    const bool valid = vc < NC;
+    const int seg = valid ? vc / C : 0, c = valid ? vc - seg * C : 0;
+    const int64_t ch0 = seg_chunk[seg], ch1 = seg_chunk[seg + 1];
+    const double s = block_chunk_sum(part, rows, C, blockIdx.y, c, ch0, ch1, valid);
+    if (valid && threadIdx.x < 64) part[((size_t)ch0 * rows + blockIdx.y) * C + c] = s;
+}
+
+// Scalars of step i per virtual column: beta_i, alpha_{i-1}, breakdown, and the
+// coefficients of the sweep (cf: r -= cf_l slot_l; ec: u_{i+1} -= ec_l slot_l;
+// cu, cr: the weights of u_i and r in u_{i+1}).  i = k: only beta_k and alpha_{k-1}.
+__global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, int i, int k,
+                                                   double eps_vec,
+                                                   const int64_t *__restrict__ seg_chunk,
+                                                   const double *__restrict__ part,
+                                                   double *__restrict__ nu, double *__restrict__ sig,
+                                                   double *__restrict__ alpha,
+                                                   double *__restrict__ beta,
+                                                   double *__restrict__ cf, double *__restrict__ ec,
+                                                   double *__restrict__ cu, double *__restrict__ cr,
+                                                   double *__restrict__ runmax,
+                                                   int32_t *__restrict__ active,
+                                                   int32_t *__restrict__ kused, int ku_ld, int ku_off)
+{
+    extern __shared__ double sh[];   // h[i][64], then red[2][8][64]
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int NC = nseg * C;
+    const int vc = blockIdx.x * 64 + lane;
+    const bool valid = vc < NC;
+    const int v = valid ? vc : 0;
+    const int seg = v / C, c = v - seg * C;
+    const double *S = part + (size_t)seg_chunk[seg] * rows * C + c;
+    auto at = [&](const double *a, int l) { return a[(size_t)l * NC + v]; };
+    for (int l = w; l < i; l += 8) sh[l * 64 + lane] = S[(size_t)(1 + l) * C] * at(sig, l);
+    __syncthreads();
+    auto h = [&](int l) { return sh[l * 64 + lane]; };
+    const double hl = i > 0 ? h(i - 1) : 0.0;
+    const double a_last = i > 0 ? at(alpha, i - 1) + hl : 0.0;   // alpha_{i-1}
+    auto tl = [&](int l) {
+        double t = (l == i - 1 ? a_last : at(alpha, l)) * h(l);
+        if (l + 1 < i) t += at(beta, l + 1) * h(l + 1);
+        if (l >= 1) t += at(beta, l) * h(l - 1);
+        return t;
+    };
+    double hh = 0.0, ht = 0.0;
+    for (int l = w; l < i; l += 8) {
+        hh += h(l) * h(l);
+        ht += h(l) * tl(l);
+    }
+    double *red = sh + (size_t)i * 64;
+    red[w * 64 + lane] = hh;
+    red[(8 + w) * 64 + lane] = ht;
+    __syncthreads();
+    hh = ht = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        hh += red[q * 64 + lane];
+        ht += red[(8 + q) * 64 + lane];
+    }
+    const double uu = S[0];
+    const bool was = i == 0 ? uu > 0.0 : active[v] != 0;
+    const double n2 = fmax(uu - hh, 0.0), b = sqrt(n2);
+    // the breakdown test of k_norm_fin
+    double rm = 0.0;
+    bool on = was;
+    if (i > 0) {
+        rm = fmax(runmax[v], was ? fabs(a_last) : 0.0);
+        if (i > 1) rm = fmax(rm, at(beta, i - 1));
+        on = was && b > 1e3 * eps_vec * rm;
+    }
+    const double sg = on ? 1.0 / b : 0.0;
+    const bool more = i < k;
+    const double ah = (on && more) ? (S[(size_t)(i + 1) * C] - ht - 2.0 * hl * uu) / n2 : 0.0;
+    if (more && valid) {
+        for (int l = w; l < i; l += 8) {
+            const double sl = at(sig, l);
+            cf[(size_t)l * NC + v] = on ? h(l) * sl : 0.0;
+            ec[(size_t)l * NC + v] = on ? (sg * tl(l) + (l == i - 1 ? b : 0.0)) * sl : 0.0;
+        }
+    }
+    // every read of the arrays written below is done
+    __syncthreads();
+    if (!valid || w != 0) return;
+    if (i == 0) {
+        nu[v] = uu;
+        beta[v] = 0.0;
+        kused[(size_t)seg * ku_ld + ku_off + c] = on ? k : 0;
+    } else {
+        alpha[(size_t)(i - 1) * NC + v] = was ? a_last : 0.0;
+        beta[(size_t)i * NC + v] = was ? b : 0.0;
+        if (was && !on) kused[(size_t)seg * ku_ld + ku_off + c] = i;
+    }
+    runmax[v] = rm;
+    active[v] = on ? 1 : 0;
+    sig[(size_t)i * NC + v] = sg;
+    if (more) {
+        alpha[(size_t)i * NC + v] = ah;
+        cu[v] = sg * hl;
+        cr[v] = ah * sg;
+    }
+}
+
+// The sweep of step i.  A workgroup of W wavefronts takes one row chunk of one
+// 64-column tile; wavefront w owns slots w*NB.. (at most NB of the i), its
+// coefficients and running dots in registers.  Per R rows each wavefront adds
+// its slots' part of r and u_{i+1}; the parts meet in LDS (one barrier, two
+// buffers), every wavefront forms the same r and u_{i+1} and takes the dots
+// with its own slots, which are still in registers.
+template <int NB, int R>
+__global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int nseg,
+                                               const int64_t *__restrict__ seg_row,
+                                               const int64_t *__restrict__ seg_chunk,
+                                               double *__restrict__ basis, size_t ss, int i,
+                                               const double *__restrict__ Z,
+                                               const double *__restrict__ sig,
+                                               const double *__restrict__ cf,
+                                               const double *__restrict__ ec,
+                                               const double *__restrict__ cu,
+                                               const double *__restrict__ cr, int store_u, int rows,
+                                               double *__restrict__ part)
+{
+    extern __shared__ double2 xch[];   // [2][W][R][64]
+    constexpr int NA = NB > 0 ? NB : 1;
+    const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
+    const int ct = (int)(L % nct);
+    const int64_t chunk = L / nct;
+    const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6), W = uniform(blockDim.x >> 6);
+    const int craw = ct * 64 + lane;
+    const bool colok = craw < C;
+    const int c = colok ? craw : C - 1;   // lanes past the last column repeat it and store nothing
+    const int seg = find_seg(seg_chunk, nseg, chunk);
+    const int64_t r0 = seg_row[seg] + (chunk - seg_chunk[seg]) * rpc;
+    const int64_t r1 = min(seg_row[seg + 1], r0 + rpc);
+    const size_t NC = (size_t)nseg * C, vc = (size_t)seg * C + c;
+    const int l0 = w * NB, nb = min(NB, i - l0);   // nb < NB only in the last wavefront
+    double co[NA], eo[NA], acc[NA];
+    size_t so[NA];
+#pragma unroll
+    for (int l = 0; l < NB; ++l) {
+        const bool ok = l < nb;
+        const int s = ok ? l0 + l : l0;
+        co[l] = ok ? cf[(size_t)s * NC + vc] : 0.0;
+        eo[l] = ok ? ec[(size_t)s * NC + vc] : 0.0;
+        so[l] = (size_t)s * ss;
+        acc[l] = 0.0;
+    }
+    const double wz = sig[(size_t)i * NC + vc], wu = cu[vc], wr = cr[vc];
+    double *U = basis + (size_t)i * ss, *UN = U + ss;
+    double accr = 0.0, accu = 0.0;
+    int buf = 0;
+    for (int64_t r = r0; r < r1; r += R) {
+        double u[R], z[R], q[R][NA];
+        size_t e[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            e[j] = (size_t)min(r + j, r1 - 1) * C + c;
+            u[j] = U[e[j]];
+            z[j] = Z[e[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int l = 0; l < NB; ++l) q[j][l] = __builtin_nontemporal_load(basis + so[l] + e[j]);
+        __builtin_amdgcn_sched_barrier(0);
+        double rr[R], un[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            double a = 0.0, b = 0.0;
+#pragma unroll
+            for (int l = 0; l < NB; ++l) {
+                a += co[l] * q[j][l];
+                b += eo[l] * q[j][l];
+            }
+            rr[j] = a;
+            un[j] = b;
+        }
+        if (W > 1) {
+            double2 *x = xch + (size_t)buf * W * R * 64;
+#pragma unroll
+            for (int j = 0; j < R; ++j) x[(w * R + j) * 64 + lane] = make_double2(rr[j], un[j]);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                double a = 0.0, b = 0.0;
+                for (int q2 = 0; q2 < W; ++q2) {
+                    const double2 p = x[(q2 * R + j) * 64 + lane];
+                    a += p.x;
+                    b += p.y;
+                }
+                rr[j] = a;
+                un[j] = b;
+            }
+            buf ^= 1;
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const bool live = r + j < r1;
+            const double rv = u[j] - rr[j];
+            double uv = wz * z[j] - wu * u[j] - un[j];
+            uv -= wr * rv;
+            if (w == 0 && live && colok) {
+                U[e[j]] = rv;
+                if (store_u) UN[e[j]] = uv;
+            }
+            uv = live ? uv : 0.0;
+#pragma unroll
+            for (int l = 0; l < NB; ++l) acc[l] += q[j][l] * uv;
+            accr += rv * uv;
+            accu += uv * uv;
+        }
+    }
+    if (!colok) return;
+    double *P = part + (size_t)chunk * rows * C + c;
+#pragma unroll
+    for (int l = 0; l < NB; ++l)
+        if (l < nb) P[(size_t)(1 + l0 + l) * C] = acc[l];
+    if (w == 0) {
+        P[0] = accu;
+        P[(size_t)(1 + i) * C] = accr;
+    }
+}
+
+// ------------------------------------------------------------------ launchers
+
+void launch_dot_uz(const Plan &p, int i, const void *z, hipStream_t st)
+{
+    k_dot_uz<<<(unsigned)((int64_t)p.nchunk * p.nct), 256, 0, st>>>(
+        p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (const double *)p.basis + (size_t)i * slot_elems(p),
+        (const double *)z, p.part_rows, i + 1, p.part);
+}
+
+void launch_sweep_fin(const Plan &p, int i, hipStream_t st)
+{
+    const int NC = p.nseg * p.C;
+    const unsigned tiles = (NC + 63) / 64;
+    const int rows = i < p.k ? i + 2 : i + 1;
+    k_sweep_sum<<<dim3(tiles, rows), 64 * kFinWaves, 0, st>>>(p.C, p.nseg, p.part_rows, p.seg_chunk, p.part);
+    k_sweep_fin<<<tiles, 512, sizeof(double) * 64 * ((size_t)i + 16), st>>>(
+        p.C, p.nseg, p.part_rows, i, p.k, DBL_EPSILON, p.seg_chunk, p.part, p.nu, p.sig, p.alpha, p.beta,
+        p.cf, p.ec, p.cu, p.cr, p.runmax, p.active, p.kused, p.Ct, p.c_off);
+}
+
+template <int NB>
+static void sweep_t(const Plan &p, int i, int W, const void *z, hipStream_t st)
+{
+    constexpr int R = NB > 8 ? 2 : 4;
+    k_sweep<NB, R><<<(unsigned)((int64_t)p.nchunk * p.nct), 64 * W, W > 1 ? sizeof(double2) * 2 * W * R * 64 : 0, st>>>(
+        p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (double *)p.basis, slot_elems(p), i,
+        (const double *)z, p.sig, p.cf, p.ec, p.cu, p.cr, i + 1 < p.k ? 1 : 0, p.part_rows, p.part);
+}
+
+void launch_sweep(const Plan &p, int i, const void *z, hipStream_t st)
+{
+    const int W = i > kSweepSlots ? (i + kSweepSlots - 1) / kSweepSlots : 1;
+    const int nb = (i + W - 1) / W;
+    switch (nb) {
+#define ECNT_CASE(N)              \
+    case N:                       \
+        sweep_t<N>(p, i, W, z, st); \
+        break;
+        ECNT_CASE(0) ECNT_CASE(1) ECNT_CASE(2) ECNT_CASE(3) ECNT_CASE(4) ECNT_CASE(5)
+        ECNT_CASE(6) ECNT_CASE(7) ECNT_CASE(8) ECNT_CASE(9) ECNT_CASE(10) ECNT_CASE(11)
+        ECNT_CASE(12) ECNT_CASE(13) ECNT_CASE(14) ECNT_CASE(15) ECNT_CASE(16)
+#undef ECNT_CASE
+    default:
+        break;
+    }
+}
+
+}  // namespace ecnt

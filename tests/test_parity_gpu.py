@@ -694,6 +694,24 @@ def test_smooth_rejects_unsupported(ec):
     assert e.value.status == ec.ECNT_EUNSUPPORTED
 
 
+@pytest.mark.parametrize("k", [1, 2, 16, 17, 33, 49, 112, 113])
+@pytest.mark.parametrize("prec,m,cols", [("cheb", 3, 0), ("jacobi", 37, 0), ("cheb", 37, 50)])
+def test_one_sweep_step_edges(ec, prec, m, cols, k):
+    """The one-sweep Lanczos step against the oracle where its split changes:
+    one to seven wavefronts of at most 16 slots, a wavefront with fewer slots
+    than the others, one and two column tiles (the last one ragged), column
+    waves, and k = 113, which the two-read form takes.  n = 693: rows that no
+    chunk divides.  s_j is within the oracle's rounding times the conditioning
+    of the rule, well below 1e-10 |v_j|^2; alpha and beta lose digits once Ritz
+    values converge, so they are compared up to k = 33."""
+    wl = W.Workload("e", (9, 7, 11), "wells", 5, -8.0, -2.0, prec, m, k)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)
+    r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, k, tune={"fused": "off"}, max_cols=cols)
+    ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V, k)
+    assert_parity(r, ref, k if k <= 33 else None, probe_scale="nu")
+
+
 # ---------------------------------------------------------------------------
 # A as a grid stencil (a_form auto) against the CSR sweep (a_form csr)
 # ---------------------------------------------------------------------------
