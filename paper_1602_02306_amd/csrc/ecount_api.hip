@@ -196,9 +196,6 @@ size_t plan_layout(Plan &p, char *base)
         p.g_tbar = (double *)take(blk);
         p.g_gall = (double *)take(sizeof(double) * k * k * C);
         p.g_pall = (double *)take(sizeof(double) * k * k * C);
-        p.g_Z = (double *)take(sizeof(double) * k * k * C);
-        p.g_theta = (double *)take(sizeof(double) * k * C);
-        p.g_sval = (double *)take(sizeof(double) * k * C);
         p.g_abar = (double *)take(sizeof(double) * k * C);
         p.g_bbar = (double *)take(sizeof(double) * (k + 1) * C);
         p.g_coef = (double *)take(sizeof(double) * 4 * 32 * C);

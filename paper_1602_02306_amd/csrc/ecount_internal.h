@@ -149,9 +149,6 @@ struct Plan {
     double *g_tbar = nullptr;  // block: M ybar
     double *g_gall = nullptr;  // k*k*C: update coefficients c_i[l] of every step
     double *g_pall = nullptr;  // k*k*C: Gram column q_l^T q_i - [l = i] of every step
-    double *g_Z = nullptr;     // k*k*C: eigenvectors of J
-    double *g_theta = nullptr; // k*C
-    double *g_sval = nullptr;  // k*C
     double *g_abar = nullptr;  // k*C
     double *g_bbar = nullptr;  // (k+1)*C
     double *g_coef = nullptr;  // 4*32*C

@@ -36,120 +36,136 @@ __device__ __forceinline__ double smooth_step_d(double th, double w)
 }
 
 // ---- tridiagonal adjoint: full eigendecomposition of J_ku, then alphabar, betabar ----
-// Z (k x k per column) lives in global scratch at Z[(a*k + b)*C + c].
+// One wavefront per column (k <= 32): implicit QR with Wilkinson shifts as in
+// the quadrature's wavefront form, every lane running the rotation chain and
+// lane r carrying row r of Z through it (both halves of the wavefront repeat
+// the rows).  Then, with F = S[1] o z z^T, u^(l) = F Z[l], lane a holding row a
+// of F: alphabar_l = scale Z[l].u^(l), betabar_{l+1} = 2 scale Z[l-1].u^(l); the
+// halves take even and odd l.  Bound: the sequential rotations (about 1.6 k^2).
+// With a lane per column and Z in global memory 64 columns of k = 30 took 19 ms.
 __global__ __launch_bounds__(64) void k_tridiag_bwd(int C, int k, int m, double smooth_w,
                                                     double g_out,
                                                     const double *__restrict__ alpha,
                                                     const double *__restrict__ beta,
                                                     const int32_t *__restrict__ kused,
                                                     const double *__restrict__ nu,
-                                                    double *__restrict__ Zg, double *__restrict__ th,
-                                                    double *__restrict__ sv,
                                                     double *__restrict__ abar,
                                                     double *__restrict__ bbar,
                                                     int32_t *__restrict__ flags)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-#define Z_(a, b) Zg[((size_t)(a) * k + (b)) * C + c]
-#define A_(i) th[(size_t)(i) * C + c]
-    // offdiagonal kept in bbar during the iteration, overwritten at the end
-#define B_(i) bbar[(size_t)(i) * C + c]
+    __shared__ double A_[kBasisChunk + 1], B_[kBasisChunk + 1], Sv[kBasisChunk];
+    __shared__ double Z_[kBasisChunk * 32];   // column b, row r at b * 32 + r
+    const int c = blockIdx.x, lane = threadIdx.x, row = lane & 31, half = lane >> 5;
     const int N = kused[c];
-    for (int i = 0; i <= k; ++i) B_(i) = 0.0;
-    for (int i = 0; i < k; ++i) abar[(size_t)i * C + c] = 0.0;
-    if (N < 1) return;
-    for (int i = 0; i < N; ++i) {
-        A_(i) = alpha[(size_t)i * C + c];
-        if (i + 1 < N) B_(i) = beta[(size_t)(i + 1) * C + c];
-        for (int j = 0; j < N; ++j) Z_(i, j) = i == j ? 1.0 : 0.0;
+    for (int i = lane; i <= k; i += 64) {
+        if (i < k && (N < 1 || i >= N)) abar[(size_t)i * C + c] = 0.0;
+        if (i == 0 || N < 1 || i >= N) bbar[(size_t)i * C + c] = 0.0;
     }
+    if (N < 1) return;
+    if (lane < N) {
+        A_[lane] = alpha[(size_t)lane * C + c];
+        B_[lane] = lane + 1 < N ? beta[(size_t)(lane + 1) * C + c] : 0.0;
+    }
+    for (int b = half; b < 32; b += 2) Z_[b * 32 + row] = b == row ? 1.0 : 0.0;
+    __syncthreads();
     int hi = N - 1, iter = 0;
     bool failed = false;
     while (hi > 0) {
-        if (fabs(B_(hi - 1)) <= DBL_EPSILON * (fabs(A_(hi - 1)) + fabs(A_(hi))) ||
-            fabs(B_(hi - 1)) < DBL_MIN) {
-            B_(hi - 1) = 0.0;
+        if (fabs(B_[hi - 1]) <= DBL_EPSILON * (fabs(A_[hi - 1]) + fabs(A_[hi])) ||
+            fabs(B_[hi - 1]) < DBL_MIN) {
+            __syncthreads();
+            B_[hi - 1] = 0.0;
+            __syncthreads();
             --hi;
             continue;
         }
-        int lo = hi - 1;
-        while (lo > 0) {
-            const double bl = fabs(B_(lo - 1));
-            if (bl <= DBL_EPSILON * (fabs(A_(lo - 1)) + fabs(A_(lo))) || bl < DBL_MIN) {
-                B_(lo - 1) = 0.0;
-                break;
+        int lo = 0;
+        {
+            const int i = hi - 1 - row;
+            bool neg = false;
+            if (i >= 1) {
+                const double bl = fabs(B_[i - 1]);
+                neg = bl <= DBL_EPSILON * (fabs(A_[i - 1]) + fabs(A_[i])) || bl < DBL_MIN;
             }
-            --lo;
+            const unsigned msk = (unsigned)__ballot(neg);
+            if (msk) lo = hi - 1 - (__ffs((int)msk) - 1);
         }
         if (++iter > 60 * N) {
             failed = true;
             break;
         }
-        const double bb = B_(hi - 1);
-        const double d = 0.5 * (A_(hi - 1) - A_(hi));
+        const double bb = B_[hi - 1];
+        const double d = 0.5 * (A_[hi - 1] - A_[hi]);
         const double den = d + copysign(hypot(d, bb), d);
-        const double mu = A_(hi) - (den != 0.0 ? bb * bb / den : 0.0);
-        double x = A_(lo) - mu, y = B_(lo);
+        const double mu = A_[hi] - (den != 0.0 ? bb * bb / den : 0.0);
+        double x = A_[lo] - mu, y = B_[lo];
+        double ak = A_[lo], bk = B_[lo], zk = Z_[lo * 32 + row], nbk = bk;
+        // values ahead of the rotation (written by no rotation before theirs)
+        double a1 = A_[lo + 1], b1 = lo + 1 < hi ? B_[lo + 1] : 0.0, z1 = Z_[(lo + 1) * 32 + row];
         for (int kk = lo; kk < hi; ++kk) {
-            const double r = hypot(x, y);
-            double cs = 1.0, sn = 0.0;
-            if (r > 0.0) {
-                cs = x / r;
-                sn = y / r;
-            }
-            if (kk > lo) B_(kk - 1) = r;
-            const double ak = A_(kk), ak1 = A_(kk + 1), bk = B_(kk);
-            A_(kk) = cs * cs * ak + 2.0 * cs * sn * bk + sn * sn * ak1;
-            A_(kk + 1) = sn * sn * ak - 2.0 * cs * sn * bk + cs * cs * ak1;
-            const double nbk = cs * sn * (ak1 - ak) + (cs * cs - sn * sn) * bk;
-            B_(kk) = nbk;
-            if (kk + 1 < hi) {
-                const double bk1 = B_(kk + 1);
-                y = sn * bk1;
-                B_(kk + 1) = cs * bk1;
-                x = nbk;
-            }
-            for (int rr = 0; rr < N; ++rr) {
-                const double z0 = Z_(rr, kk), z1 = Z_(rr, kk + 1);
-                Z_(rr, kk) = cs * z0 + sn * z1;
-                Z_(rr, kk + 1) = -sn * z0 + cs * z1;
-            }
+            const int nx = min(kk + 2, hi);
+            const double a2 = A_[nx], b2 = nx < hi ? B_[nx] : 0.0, z2 = Z_[nx * 32 + row];
+            const double q2 = x * x + y * y;
+            const bool nz = q2 > 0.0;
+            const double ir = rsqrt_pos(nz ? q2 : 1.0);
+            const double r = nz ? q2 * ir : 0.0;
+            const double cs = nz ? x * ir : 1.0;
+            const double sn = nz ? y * ir : 0.0;
+            if (kk > lo) B_[kk - 1] = r;
+            A_[kk] = cs * cs * ak + 2.0 * cs * sn * bk + sn * sn * a1;
+            const double na1 = sn * sn * ak - 2.0 * cs * sn * bk + cs * cs * a1;
+            nbk = cs * sn * (a1 - ak) + (cs * cs - sn * sn) * bk;
+            Z_[kk * 32 + row] = cs * zk + sn * z1;
+            zk = -sn * zk + cs * z1;
+            ak = na1;
+            bk = cs * b1;
+            x = nbk;
+            y = sn * b1;
+            a1 = a2;
+            b1 = b2;
+            z1 = z2;
         }
+        A_[hi] = ak;
+        B_[hi - 1] = nbk;
+        Z_[hi * 32 + row] = zk;
+        __syncthreads();
     }
-    if (failed) atomicOr(&flags[1], 1);
+    if (failed && lane == 0) atomicOr(&flags[1], 1);
+    if (lane < N) Sv[lane] = smooth_step(A_[lane], smooth_w);
+    __syncthreads();
     // seed: d estimate / d s_c = +-1/m (eta columns +, xi columns -)
     const double sbar = g_out * ((c >= m) ? 1.0 : -1.0) / (double)m;
     const double scale = sbar * nu[c];
-    for (int a = 0; a < N; ++a) sv[(size_t)a * C + c] = smooth_step(A_(a), smooth_w);
-    // u^(l)_a = sum_b F_ab Z[l][b],  F_ab = S[1](th_a, th_b) z_a z_b;  then
-    // abar_l = scale * Z[l] . u^(l),  bbar_{l+1} = 2 * scale * Z[l] . u^(l+1)
-    for (int i = 0; i <= k; ++i) B_(i) = 0.0;
-    for (int l = N - 1; l >= 0; --l) {
-        double diag = 0.0, off = 0.0;
-        for (int a = 0; a < N; ++a) {
-            const double ta = A_(a), za = Z_(0, a);
-            double ua = 0.0, uan = 0.0;
-            for (int b = 0; b < N; ++b) {
-                const double tb = A_(b);
-                double D;
-                if (fabs(ta - tb) < 1e-8 * (1.0 + fabs(ta)))
-                    D = smooth_step_d(0.5 * (ta + tb), smooth_w);
-                else
-                    D = (sv[(size_t)a * C + c] - sv[(size_t)b * C + c]) / (ta - tb);
-                const double F = D * za * Z_(0, b);
-                ua += F * Z_(l, b);
-                if (l + 1 < N) uan += F * Z_(l + 1, b);
-            }
-            diag += Z_(l, a) * ua;
-            off += Z_(l, a) * uan;
-        }
-        abar[(size_t)l * C + c] = scale * diag;
-        if (l + 1 < N) B_(l + 1) = 2.0 * scale * off;   // betabar_{l+2} (array index l+1)
+    const bool live = row < N;
+    const int ra = live ? row : 0;
+    const double ta = A_[ra], sa = Sv[ra], za = live ? Z_[ra * 32] : 0.0;
+    double F[32];
+#pragma unroll
+    for (int b = 0; b < 32; ++b) {
+        const int rb = b < N ? b : 0;
+        const double tb = A_[rb];
+        double D;
+        if (fabs(ta - tb) < 1e-8 * (1.0 + fabs(ta)))
+            D = smooth_step_d(0.5 * (ta + tb), smooth_w);
+        else
+            D = (sa - Sv[rb]) / (ta - tb);
+        F[b] = b < N ? D * za * Z_[rb * 32] : 0.0;
     }
-#undef Z_
-#undef A_
-#undef B_
+    for (int l0 = 0; l0 < N; l0 += 2) {
+        const int l = min(l0 + half, N - 1);   // the last odd one repeats a row and stores the same
+        double u = 0.0;
+#pragma unroll
+        for (int b = 0; b < 32; ++b) u += F[b] * Z_[b * 32 + l];
+        double diag = Z_[ra * 32 + l] * u, off = l > 0 ? Z_[ra * 32 + l - 1] * u : 0.0;
+        diag = row_sum16(diag);
+        off = row_sum16(off);
+        diag += __shfl_xor(diag, 16, 64);
+        off += __shfl_xor(off, 16, 64);
+        if (row == 0) {
+            abar[(size_t)l * C + c] = scale * diag;
+            if (l > 0) bbar[(size_t)l * C + c] = 2.0 * scale * off;   // betabar_{l+1}
+        }
+    }
 }
 
 // ---- backward dots: raw[s] = slot_s . qbar_{i+1} (s = 0..i), raw[i+1+s] = slot_s . slot_i (s < i)
@@ -191,16 +207,15 @@ __global__ __launch_bounds__(64) void k_bdots(int64_t n, int C, int nct, int64_t
     }
 }
 
-// sums[row][c] = sum over chunks of part[chunk][row][c], one thread per (row, c)
-__global__ void k_rowsum(int C, int nchunk, int nrows, const double *__restrict__ part,
-                         double *__restrict__ sums)
+// sums[row][c] = sum over chunks of part[chunk][row][c]: a workgroup per row and
+// 64 columns (a thread per sum, its 2048 chunks in sequence, took 0.5 ms)
+__global__ __launch_bounds__(64 * kFinWaves) void k_rowsum(int C, int nchunk,
+                                                           const double *__restrict__ part,
+                                                           double *__restrict__ sums)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nrows * C) return;
-    const int row = idx / C, c = idx % C;
-    double t = 0.0;
-    for (int ch = 0; ch < nchunk; ++ch) t += part[((size_t)ch * 64 + row) * C + c];
-    sums[idx] = t;
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+    const double t = block_chunk_sum(part, kPartRows, C, blockIdx.y, c, 0, nchunk, c < C);
+    if (c < C && threadIdx.x < 64) sums[(size_t)blockIdx.y * C + c] = t;
 }
 
 // Per column: finish betabar_{i+1}, form the coefficients of rbar and gbar.
@@ -209,8 +224,8 @@ __global__ void k_rowsum(int C, int nchunk, int nrows, const double *__restrict_
 // scal[2][c] = -alpha_i sig_{i-1} (lambda: slot_{i-1} weight folded into w),
 // scal[3][c] = alphabar sig_{i-1} (mu: slot_{i-1} weight of the alphabar term of wbar),
 // scal[4][c] = -alpha_i.
-__global__ void k_bdots_fin(int C, int k, int nchunk, int i, int have_dots,
-                            const double *__restrict__ part, const double *__restrict__ sig,
+__global__ __launch_bounds__(512) void k_bdots_fin(int C, int k, int i, int have_dots,
+                            const double *__restrict__ sums, const double *__restrict__ sig,
                             const double *__restrict__ beta, const double *__restrict__ alpha,
                             const double *__restrict__ gall, const double *__restrict__ pall,
                             const double *__restrict__ abar, double *__restrict__ bbar,
@@ -218,30 +233,37 @@ __global__ void k_bdots_fin(int C, int k, int nchunk, int i, int have_dots,
                             double *__restrict__ cW, double *__restrict__ cG,
                             double *__restrict__ cR, double *__restrict__ scal)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
+    // 64 columns; the slots of a column are spread over the 8 wavefronts
+    __shared__ double red[8][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int craw = blockIdx.x * 64 + lane;
+    const bool ok = craw < C;
+    const int c = ok ? craw : C - 1;
     const int ku = kused[c];
     double a = 0.0, b = 0.0;
     const double sgi = sig[(size_t)i * C + c];
-    // part holds the chunk-summed dots here (k_rowsum)
-    auto raw = [&](int row) { return part[(size_t)row * C + c]; };
-    (void)nchunk;
-    if (have_dots && i < ku) {
+    auto raw = [&](int row) { return sums[(size_t)row * C + c]; };
+    const bool on = have_dots && i < ku;
+    if (on) {
         const double bi1 = beta[(size_t)i * C + c];                  // beta_{i+1}
         const double cc = sgi * raw(i);                              // qbar_{i+1}^T q_{i+1}
-        double bb = bbar[(size_t)i * C + c] - cc / bi1;              // betabar_{i+1}
-        bbar[(size_t)i * C + c] = bb;
         a = 1.0 / bi1;
-        b = bb;
+        b = bbar[(size_t)i * C + c] - cc / bi1;                      // betabar_{i+1}
     }
     auto cbar = [&](int s) {   // -q_s^T rbar
         if (a == 0.0 && b == 0.0) return 0.0;
         const double sg = sig[(size_t)s * C + c];
         return -(a * sg * raw(s) + b * sg * sgi * raw(i + 1 + s));
     };
+    double t = 0.0;
+    for (int s = wv; s < i; s += 8) t += pall[((size_t)(i - 1) * k + s) * C + c] * cbar(s);
+    red[wv][lane] = t;
+    __syncthreads();   // and every read of bbar above is done
     double ab = i <= ku ? abar[(size_t)(i - 1) * C + c] : 0.0;
-    for (int s = 0; s < i; ++s) ab -= pall[((size_t)(i - 1) * k + s) * C + c] * cbar(s);
-    for (int s = 0; s < i; ++s) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) ab -= red[q][lane];
+    if (!ok) return;
+    for (int s = wv; s < i; s += 8) {
         const double sg = sig[(size_t)s * C + c];
         double gb = cbar(s);
         if (s == i - 1) gb += ab;
@@ -251,6 +273,8 @@ __global__ void k_bdots_fin(int C, int k, int nchunk, int i, int have_dots,
         cG[(size_t)s * C + c] = gb;
         cR[(size_t)s * C + c] = cl;
     }
+    if (wv != 0) return;
+    if (on) bbar[(size_t)i * C + c] = b;
     const double al = alpha[(size_t)(i - 1) * C + c];
     const double sgq = sig[(size_t)(i - 1) * C + c];
     scal[c] = a;
@@ -339,19 +363,20 @@ __global__ __launch_bounds__(256) void k_bupdate(int64_t n, int C, int nct, int6
 }
 
 // betabar_i -= sig_{i-2} * sum_chunks (wbar . slot_{i-2})
-__global__ void k_bnorm_fin(int C, int nchunk, int i, const double *__restrict__ part,
-                            const double *__restrict__ sig, double *__restrict__ bbar)
+__global__ __launch_bounds__(64 * kFinWaves) void k_bnorm_fin(int C, int nchunk, int i,
+                                                              const double *__restrict__ part,
+                                                              const double *__restrict__ sig,
+                                                              double *__restrict__ bbar)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C || i < 2) return;
-    double t = 0.0;
-    for (int ch = 0; ch < nchunk; ++ch) t += part[(size_t)ch * 64 * C + c];
-    bbar[(size_t)(i - 1) * C + c] -= sig[(size_t)(i - 2) * C + c] * t;
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+    const double t = block_chunk_sum(part, kPartRows, C, 0, c, 0, nchunk, c < C);
+    if (c < C && threadIdx.x < 64) bbar[(size_t)(i - 1) * C + c] -= sig[(size_t)(i - 2) * C + c] * t;
 }
 
 // Vbar and taubar contributions of step i: tb = M ybar_i, tq = M q_i.
-// vpart[ct][r] (+)= sum over the tile's columns of tb*tq (fixed-order lane
-// reduction); part[chunk][0][c] = sum over the chunk's rows of tb*tq.
+// vpart[ct][r] (+)= sum over the tile's columns of tb*tq (in VALU, fixed
+// order); part[chunk][0][c] = sum over the chunk's rows of tb*tq.  Four rows at
+// a time; lane j < 4 keeps the sum of row r + j.
 __global__ __launch_bounds__(64) void k_vgrad(int64_t n, int C, int nct, int64_t rpc,
                                               const double *__restrict__ tb,
                                               const double *__restrict__ tq, int first,
@@ -362,33 +387,42 @@ __global__ __launch_bounds__(64) void k_vgrad(int64_t n, int C, int nct, int64_t
     const int ct = (int)(L % nct);
     const int64_t chunk = L / nct;
     const int lane = threadIdx.x;
-    const int c = ct * 64 + lane;
-    const bool ok = c < C;
+    const int craw = ct * 64 + lane;
+    const bool ok = craw < C;
+    const int c = ok ? craw : C - 1;
     const int64_t r0 = chunk * rpc, r1 = min(n, r0 + rpc);
     double tacc = 0.0;
-    for (int64_t r = r0; r < r1; ++r) {
-        const size_t e = (size_t)r * C + c;
-        double p = ok ? tb[e] * tq[e] : 0.0;
-        tacc += p;
-        // fixed-order butterfly over the 64 lanes
+    for (int64_t r = r0; r < r1; r += 4) {
+        double *dst = vpart + (size_t)ct * n + r + lane;
+        const bool mine = lane < 4 && r + lane < r1;
+        const double old = (mine && !first) ? *dst : 0.0;
+        double x[4], y[4];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
-        if (lane == 0) {
-            double *dst = vpart + (size_t)ct * n + r;
-            *dst = first ? p : *dst + p;
+        for (int j = 0; j < 4; ++j) {
+            const size_t e = (size_t)min(r + j, r1 - 1) * C + c;
+            x[j] = tb[e];
+            y[j] = tq[e];
         }
+        double keep = 0.0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double p = (ok && r + j < r1) ? x[j] * y[j] : 0.0;
+            tacc += p;
+            const double t = wave_sum_dpp(p);
+            keep = lane == j ? t : keep;
+        }
+        if (mine) *dst = old + keep;
     }
-    if (ok) part[(size_t)chunk * 64 * C + c] = tacc;
+    if (ok) part[(size_t)chunk * kPartRows * C + c] = tacc;
 }
 
-__global__ void k_vgrad_fin(int C, int nchunk, const double *__restrict__ part,
-                            double *__restrict__ taubar, int first)
+__global__ __launch_bounds__(64 * kFinWaves) void k_vgrad_fin(int C, int nchunk,
+                                                              const double *__restrict__ part,
+                                                              double *__restrict__ taubar, int first)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    double t = 0.0;
-    for (int ch = 0; ch < nchunk; ++ch) t += part[(size_t)ch * 64 * C + c];
-    taubar[c] = (first ? 0.0 : taubar[c]) - t;
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+    const double t = block_chunk_sum(part, kPartRows, C, 0, c, 0, nchunk, c < C);
+    if (c < C && threadIdx.x < 64) taubar[c] = (first ? 0.0 : taubar[c]) - t;
 }
 
 // dV[r] = sum_ct vpart[ct][r]
@@ -430,9 +464,8 @@ static inline unsigned red_blocks(const Plan &p)
 
 void launch_tridiag_bwd(const Plan &p, double g_out, hipStream_t st)
 {
-    k_tridiag_bwd<<<(p.C + 63) / 64, 64, 0, st>>>(p.C, p.k, p.m, p.smooth_w, g_out, p.alpha, p.beta,
-                                                   p.kused, p.nu, p.g_Z, p.g_theta, p.g_sval, p.g_abar,
-                                                   p.g_bbar, p.flags);
+    k_tridiag_bwd<<<p.C, 64, 0, st>>>(p.C, p.k, p.m, p.smooth_w, g_out, p.alpha, p.beta, p.kused,
+                                      p.nu, p.g_abar, p.g_bbar, p.flags);
 }
 
 #define ECNT_NS_CASES(F)                                                                        \
@@ -462,9 +495,9 @@ void launch_bdots_fin(const Plan &p, int i, bool have_dots, hipStream_t st)
     const size_t C = p.C;
     if (have_dots) {
         const int rows = 2 * i + 1;
-        k_rowsum<<<(rows * p.C + 255) / 256, 256, 0, st>>>(p.C, p.nchunk, rows, p.part, p.g_sums);
+        k_rowsum<<<dim3((p.C + 63) / 64, rows), 64 * kFinWaves, 0, st>>>(p.C, p.nchunk, p.part, p.g_sums);
     }
-    k_bdots_fin<<<(p.C + 255) / 256, 256, 0, st>>>(p.C, p.k, p.nchunk, i, have_dots ? 1 : 0,
+    k_bdots_fin<<<(p.C + 63) / 64, 512, 0, st>>>(p.C, p.k, i, have_dots ? 1 : 0,
                                                    p.g_sums, p.sig, p.beta, p.alpha, p.g_gall,
                                                    p.g_pall, p.g_abar,
                                                    p.g_bbar, p.kused, p.g_coef, p.g_coef + 32 * C,
@@ -504,7 +537,8 @@ void launch_bupdate(const Plan &p, int i, bool first, hipStream_t st)
 
 void launch_bnorm_fin(const Plan &p, int i, hipStream_t st)
 {
-    k_bnorm_fin<<<(p.C + 255) / 256, 256, 0, st>>>(p.C, p.nchunk, i, p.part, p.sig, p.g_bbar);
+    if (i < 2) return;   // beta_1 = 0 has no adjoint
+    k_bnorm_fin<<<(p.C + 63) / 64, 64 * kFinWaves, 0, st>>>(p.C, p.nchunk, i, p.part, p.sig, p.g_bbar);
 }
 
 void launch_vgrad(const Plan &p, const double *tq, bool first, hipStream_t st)
@@ -512,7 +546,7 @@ void launch_vgrad(const Plan &p, const double *tq, bool first, hipStream_t st)
     const int nct = (p.C + 63) / 64;
     k_vgrad<<<red_blocks(p), 64, 0, st>>>(p.n, p.C, nct, p.rpc, p.g_tbar, tq, first ? 1 : 0,
                                           p.g_vpart, p.part);
-    k_vgrad_fin<<<(p.C + 255) / 256, 256, 0, st>>>(p.C, p.nchunk, p.part, p.g_taubar, first ? 1 : 0);
+    k_vgrad_fin<<<(p.C + 63) / 64, 64 * kFinWaves, 0, st>>>(p.C, p.nchunk, p.part, p.g_taubar, first ? 1 : 0);
 }
 
 void launch_grad_out(const Plan &p, double *dV, hipStream_t st)

@@ -616,6 +616,19 @@ def test_smooth_gradient_at_largest_k_several_tiles(ec, k):
     _grad_vs_oracle(ec, P, wl.xi, wl.eta, W.make_probes(wl), k, 0.05, 21)
 
 
+@pytest.mark.parametrize("m", [1, 33])
+@pytest.mark.parametrize("k", [1, 2, 3, 31])
+def test_smooth_gradient_smallest_and_ragged(ec, k, m):
+    """The reverse kernels at their edges: orders 1 to 31 of the tridiagonal
+    adjoint, one and two column tiles (the last one ragged), 210 rows (chunks
+    that are no multiple of four rows).  A wide step keeps every derivative far
+    from zero; the tolerances are those of the other gradient tests."""
+    wl = W.Workload("g", (5, 6, 7), "wells", 2, -8.0, -2.0, "cheb", m, k, smooth_w=0.5)
+    P = W.make_problem(wl)
+    print("case grad 5x6x7 m=%d k=%d" % (m, k), flush=True)
+    _grad_vs_oracle(ec, P, wl.xi, wl.eta, W.make_probes(wl), k, 0.5, 31)
+
+
 def test_smooth_gradient_hard_shift_k32(ec):
     """k = 32, 128 columns, on the n = 640 problem with xi just above the 41st
     eigenvalue (near the bottom of the spectrum, where a Gram-Schmidt pass
