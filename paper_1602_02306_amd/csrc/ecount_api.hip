@@ -153,6 +153,8 @@ size_t plan_layout(Plan &p, char *base)
     p.st_coff = (double *)take(p.stencil_a ? sizeof(double) : 0);
     p.e_blk = (double *)take(p.prec_kind == ECNT_PREC_LDL ? sizeof(double) * 2 * p.S * p.n : 0);
     p.band = (double *)take(p.prec_kind == ECNT_PREC_LDL ? ldl_band_bytes(p.n, p.S) : 0);
+    p.ldl_chain = (double *)take(sizeof(double) * ldl_chain_doubles(p));
+    p.ldl_carry = (double *)take(sizeof(double) * ldl_carry_doubles(p));
     p.result = (double *)take(sizeof(double) * kResStride * p.nseg);
     p.active = (int32_t *)take(sizeof(int32_t) * NC);
     p.kused = (int32_t *)take(sizeof(int32_t) * NCt);
@@ -533,6 +535,7 @@ static ecnt_status set_segments(Plan &p, SegHost &sh, int nseg, const int64_t *n
     col_geometry(p);
     row_geometry(p, sh);
     plan_onesweep(p, sh);
+    if (!p.ldl_whole) ldl_plan_parts(p);
     plan_layout(p, nullptr);
     return ECNT_OK;
 }
@@ -1158,6 +1161,10 @@ static ecnt_status run(const ecnt_csr *A, const ecnt_prec *T, const double *taus
     if ((mode == 2 || mode == 3) && !dV) return fail(ECNT_EINVAL, "dV is null");
     if (mode >= 1 && mode <= 3 && A && A->val_type != ECNT_F64)
         return fail(ECNT_EUNSUPPORTED, "gradients need FP64 matrix values");
+    if (p.ldl_parts > 1 && ws_bytes < p.bytes) {   // a workspace that holds the whole form only
+        p.ldl_parts = 1;
+        plan_layout(p, nullptr);
+    }
     rc = check_common(A, probes, o, ws, p, ws_bytes);
     if (rc) return rc;
     p.val_f32 = A->val_type == ECNT_F32;
@@ -1308,6 +1315,7 @@ ecnt_status ecnt_count_noalloc(const ecnt_csr *A, const ecnt_prec *T, double xi,
         SegHost sh;
         const double taus[2] = {xi, eta};
         ecnt_status rc = make_plan(p, A ? A->n : 0, m, 2, T, opts);
+        p.ldl_whole = 1;   // the least that the count needs (ecnt_count takes more where it fits)
         if (!rc) rc = single_segment(p, sh, taus);
         if (!rc) rc = check_common(A, probes, opts, (void *)&p, p, p.bytes);
         if (rc) return rc;

@@ -123,6 +123,10 @@ struct Plan {
     LdlDev ldl[kMaxShifts];
     double *e_blk = nullptr;   // S * 2n: e_diag then e_off of every shift
     double *band = nullptr;    // S * 2 * n * 256: rows of L and of L^T by distance
+    int ldl_parts = 1;         // parts of the rows in a triangular solve
+    int ldl_whole = 0;         // 1: one part whatever the size (a workspace of the small form)
+    double *ldl_chain = nullptr; // S * 2 * (parts - 2) * 256 * 256: K_p
+    double *ldl_carry = nullptr; // 2 * parts * C * 256: carried-in sums of every part, corrections
     // ---- Arnoldi estimator for an unfactored T (one problem) ----
     int arnoldi = 0;
     double *H = nullptr;       // k x (k+1) x NC: H[(l*(k+1) + i)*NC + vc] = h_{i+1,l+1}
@@ -252,6 +256,10 @@ void launch_blk_quad(const Plan &p, hipStream_t st);
 void launch_ldl_eblocks(const Plan &p, hipStream_t st);
 void launch_ldl(const Plan &p, int what, const void *X, const double *xs, void *Y, hipStream_t st);
 int ldl_ring_rows();
+void ldl_plan_parts(Plan &p);
+int64_t ldl_part_rows(int64_t n, int P);
+size_t ldl_chain_doubles(const Plan &p);
+size_t ldl_carry_doubles(const Plan &p);
 size_t ldl_band_bytes(int64_t n, int S);   // the band forms of S factors, with their padding
 
 // bandwidth probes (k_probe.hip): 0 copy, 1 read, 2 update mix; 0 ok, -1 HIP error

@@ -142,6 +142,36 @@ def test_ldl_fp32_storage_within_bound(ec):
     assert abs(r.negcounts[0] - mean) <= 1e-4 * max(1.0, abs(mean))
 
 
+@pytest.mark.parametrize("dims,taus,m,k", [((81, 50), (300.0,), 1, 4), ((81, 50), (300.0, 900.0), 5, 3),
+                                           ((97, 83), (700.0,), 37, 3), ((71, 64), (500.0,), 16, 4)])
+def test_ldl_solves_in_parts(ec, dims, taus, m, k):
+    """Solves cut into parts of the rows (the chain of carried sums and its one
+    refinement) against the oracle: few parts and many, a ragged last part,
+    column counts that are no multiple of four, two shifts in one launch.  The
+    refined solves leave a residual of rounding, as plain substitution does, so
+    the tolerance is the other cases'."""
+    A = W.laplacian_csr(dims)
+    A.val = A.val * float((dims[0] + 1) ** 2)
+    V = W.rademacher(A.n, m, 77)
+    r, refs = run_pair(ec, A, taus, 1e-4, V, k)
+    assert_negcount_parity(r, refs, V)
+
+
+def test_ldl_parts_at_the_scratch_limit(ec):
+    """A count whose parts would not fit the fixed array runs in one part, as
+    it did before there were parts, and agrees with the parted one."""
+    dims, taus, m, k = (77, 77), (300.0, 700.0), 4, 3
+    A = W.laplacian_csr(dims)
+    A.val = A.val * float((dims[0] + 1) ** 2)
+    prec = ec.ildl_precond(A, taus, 1e-4)
+    assert ec.workspace_bytes(A.n, m, 2, prec, k) > ec.NOALLOC_SCRATCH_BYTES
+    Ad = ec.upload_csr(A)
+    V = torch.from_numpy(W.rademacher(A.n, m, 78)).cuda()
+    a = ec.count(Ad, prec, taus[0], taus[1], V, k)
+    b = ec.count_noalloc(Ad, prec, taus[0], taus[1], V, k)
+    assert float((a.per_probe - b.per_probe).abs().max()) <= 1e-10 * float(b.per_probe.abs().max())
+
+
 def test_ldl_table1_full_size(ec):
     """Table 1, Laplace (127 x 127, tau = 3000, m = 50) at the bench's
     configuration: parity with the oracle, and the estimate within the 5% of
