@@ -478,6 +478,11 @@ static void plan_onesweep(Plan &p, SegHost &sh)
     p.onesweep = 0;
     p.part_rows = kPartRows;
     if (p.vec_f32 || p.grad || p.arnoldi || p.block || p.k > kSweepMaxK) return;
+    // a smoothed count that the differentiated form also serves returns the
+    // same estimate as its forward: the same form computes both
+    if (p.smooth_w > 0.0 && p.rule == ECNT_RULE_GAUSS && p.prec_kind == ECNT_PREC_CHEB_LAPLACIAN &&
+        p.k <= kBasisChunk && p.wave_cols == p.Ct)
+        return;
     const size_t most = plan_layout(p, nullptr);
     const int64_t rpc = p.rpc;
     const std::vector<int64_t> chunk = sh.chunk;
