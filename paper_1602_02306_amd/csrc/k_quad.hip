@@ -13,15 +13,11 @@
 
 #include "device_common.h"
 #include "ecount_internal.h"
+#include "tridiag_dc.h"
 
 namespace ecnt {
 
-constexpr int kQuadLdsBytes = 48 * 1024;
-
-template <int KMAX>
-struct QuadGeom {
-    static constexpr int lanes = (kQuadLdsBytes / (24 * KMAX)) < 64 ? (kQuadLdsBytes / (24 * KMAX)) : 64;
-};
+constexpr int kQrOrder = 16;   // largest order of the lane-per-column form
 
 __device__ __forceinline__ double step_fn(double th, double w)
 {
@@ -31,11 +27,10 @@ __device__ __forceinline__ double step_fn(double th, double w)
 
 // One lane per virtual column vc = seg*C + c (alpha, beta, nu indexed [row][NC]);
 // kused, s_out and minabs are global: [seg*ld + off + c].  A workgroup is
-// blockDim.x lanes (at most QuadGeom<KMAX>::lanes): the columns' QR
+// blockDim.x lanes: the columns' QR
 // iterations diverge, so a wavefront runs as long as the union of its lanes'
 // paths, and few columns go one to a wavefront (the launcher's choice).  The
-// matrices live in dynamic LDS, 3 * KMAX doubles per lane.
-template <int KMAX>
+// matrices live in dynamic LDS, 3 * kQrOrder doubles per lane.
 __global__ __launch_bounds__(64) void k_tridiag(int NC, int C, int ld, int off, int k, int rule,
                                                 double smooth_w,
                                                 const double *__restrict__ alpha,
@@ -56,8 +51,8 @@ __global__ __launch_bounds__(64) void k_tridiag(int NC, int C, int ld, int off, 
     const int c = vc;
     C = NC;   // alpha, beta, nu below are indexed [row][NC] by the virtual column
     double *a = lds + lane;
-    double *b = lds + KMAX * LN + lane;
-    double *z = lds + 2 * KMAX * LN + lane;
+    double *b = lds + kQrOrder * LN + lane;
+    double *z = lds + 2 * kQrOrder * LN + lane;
 #define A_(i) a[(i) * LN]
 #define B_(i) b[(i) * LN]
 #define Z_(i) z[(i) * LN]
@@ -243,14 +238,10 @@ __global__ __launch_bounds__(256) void k_reduce(int S, int m, const double *__re
     if (threadIdx.x == 0) res[3 * S - 2] = sh[0];
 }
 
-// The same eigensolve with one wavefront per column (few columns): every lane
-// runs the rotation chain on the same values, the search for the unreduced
-// block takes 64 candidates at a time (a ballot), and each sweep carries its
-// changing values in registers with the values ahead loaded three rotations
-// early, as the lane form does.  A rotation's writes come from every lane (the
-// same values to the same slots); lane 0 makes the others.
-template <int KMAX>
-__global__ __launch_bounds__(64) void k_tridiag_wave(int NC, int C, int ld, int off, int k, int rule,
+// The same quadrature by divide and conquer (tridiag_dc.h), one workgroup of
+// P NMAX threads per column.
+template <int NMAX, int P>
+__global__ __launch_bounds__(NMAX * P) void k_tridiag_dc(int NC, int C, int ld, int off, int k, int rule,
                                                      double smooth_w,
                                                      const double *__restrict__ alpha,
                                                      const double *__restrict__ beta,
@@ -260,183 +251,117 @@ __global__ __launch_bounds__(64) void k_tridiag_wave(int NC, int C, int ld, int 
                                                      double *__restrict__ minabs_all,
                                                      int32_t *__restrict__ flags)
 {
-    __shared__ double A_[KMAX + 1], B_[KMAX + 1], Z_[KMAX + 1];
-    const int lane = threadIdx.x;
+    __shared__ DcLds<NMAX> w;
+    constexpr int kW = NMAX * P >= 64 ? NMAX * P / 64 : 1;
+    __shared__ double A_[NMAX], B_[NMAX], red[2][kW];
+    const int t = threadIdx.x;
     const int vc = blockIdx.x;
     const int seg = vc / C;
     const size_t gidx = (size_t)seg * ld + off + (vc - seg * C);
-    const int c = vc;
-    C = NC;   // alpha, beta, nu below are indexed [row][NC] by the virtual column
     const int ku = kused_all[gidx];
     if (ku < 1) {
-        if (lane == 0) {
+        if (t == 0) {
             s_all[gidx] = 0.0;
             minabs_all[gidx] = INFINITY;
         }
         return;
     }
-    int N;
-    if (rule == 1 && ku == k && k >= 2) {
-        // eq. GA_Tk: diag (a_1..a_k, a_{k-1}..a_1), off (b_2..b_k, b_{k+1}, b_{k-1}..b_2)
-        N = 2 * k - 1;
-        for (int i = lane; i < N; i += 64) {
-            A_[i] = alpha[(size_t)(i < k ? i : 2 * k - 2 - i) * C + c];
-            if (i < N - 1) B_[i] = beta[(size_t)(i < k ? i + 1 : 2 * k - 2 - i) * C + c];
-        }
-    } else {
-        N = ku;
-        for (int i = lane; i < N; i += 64) {
-            A_[i] = alpha[(size_t)i * C + c];
-            if (i < N - 1) B_[i] = beta[(size_t)(i + 1) * C + c];
-        }
+    // eq. GA_Tk: diag (a_1..a_k, a_{k-1}..a_1), off (b_2..b_k, b_{k+1}, b_{k-1}..b_2)
+    const bool ga = rule == 1 && ku == k && k >= 2;
+    const int N = ga ? 2 * k - 1 : ku;
+    double a = 0.0, b = 0.0;
+    if (t < N) {
+        a = alpha[(size_t)(t < k ? t : 2 * k - 2 - t) * NC + vc];
+        if (t + 1 < N) b = beta[(size_t)(t < k ? t + 1 : 2 * k - 2 - t) * NC + vc];
     }
-    for (int i = lane; i < N; i += 64) Z_[i] = i == 0 ? 1.0 : 0.0;
-    if (lane == 0) B_[N - 1] = 0.0;   // past the last row: what a sweep's last rotation reads
-    __syncthreads();
-
-    int hi = N - 1, iter = 0;
-    bool failed = false;
-    while (hi > 0) {
-        if (fabs(B_[hi - 1]) <= DBL_EPSILON * (fabs(A_[hi - 1]) + fabs(A_[hi])) ||
-            fabs(B_[hi - 1]) < DBL_MIN) {
-            __syncthreads();
-            if (lane == 0) B_[hi - 1] = 0.0;
-            __syncthreads();
-            --hi;
-            continue;
+    // scaled to entries of magnitude at most 1
+    const double m0 = fmax(fabs(a), fabs(b));
+    const bool bad = !(fabs(a) <= DBL_MAX) || !(fabs(b) <= DBL_MAX);
+    if (__syncthreads_or(bad)) {
+        if (t == 0) {
+            s_all[gidx] = NAN;
+            minabs_all[gidx] = NAN;
+            atomicOr(&flags[1], 1);
         }
-        // the largest lo < hi with B[lo-1] negligible (or 0), 64 candidates at a time
-        int lo = 0;
-        for (int base = hi - 1; base > 0; base -= 64) {
-            const int i = base - lane;
-            bool neg = false;
-            if (i >= 1) {
-                const double bl = fabs(B_[i - 1]);
-                neg = bl <= DBL_EPSILON * (fabs(A_[i - 1]) + fabs(A_[i])) || bl < DBL_MIN;
-            }
-            const unsigned long long msk = __ballot(neg);
-            if (msk) {
-                lo = base - (__ffsll((long long)msk) - 1);
-                break;
-            }
-        }
-        if (++iter > 60 * N) {
-            failed = true;
-            break;
-        }
-        // Wilkinson shift from the trailing 2x2 block of the active window
-        const double bb = B_[hi - 1];
-        const double d = 0.5 * (A_[hi - 1] - A_[hi]);
-        const double den = d + copysign(hypot(d, bb), d);
-        const double mu = A_[hi] - (den != 0.0 ? bb * bb / den : 0.0);
-        if (lo > 0 && lane == 0) B_[lo - 1] = 0.0;   // the split found above (not read by the sweep)
-        double x = A_[lo] - mu, y = B_[lo];
-        double ak = A_[lo], bk = B_[lo], zk = Z_[lo], nbk = bk;
-        auto rot = [&](int q, double ak1, double bk1, double z1) __attribute__((always_inline)) {
-            // |x|, |y| far from the under/overflow range: J_k holds O(|C|) entries
-            // (q2 = 0 only when x = y = 0: then r = sn = 0 as they stand)
-            const double q2 = x * x + y * y;
-            const bool nz = q2 > 0.0;
-            const double ir = rsqrt_pos(nz ? q2 : 1.0);
-            const double r = q2 * ir;
-            const double cs = nz ? x * ir : 1.0;
-            const double sn = y * ir;
-            const double na = cs * cs * ak + 2.0 * cs * sn * bk + sn * sn * ak1;
-            const double nz1 = cs * zk + sn * z1;
-            // every lane holds the same values and writes them to the same
-            // slots; the first rotation of a sweep has no B to write (slot
-            // KMAX is never read)
-            B_[q > lo ? q - 1 : KMAX] = r;
-            A_[q] = na;
-            Z_[q] = nz1;
-            const double na1 = sn * sn * ak - 2.0 * cs * sn * bk + cs * cs * ak1;
-            nbk = cs * sn * (ak1 - ak) + (cs * cs - sn * sn) * bk;
-            zk = -sn * zk + cs * z1;
-            ak = na1;
-            bk = cs * bk1;
-            x = nbk;
-            y = sn * bk1;
-        };
-        int q = lo;
-        for (const int q0 = lo + (hi - lo) % 3; q < q0; ++q) rot(q, A_[q + 1], B_[q + 1], Z_[q + 1]);
-        if (q < hi) {
-            int i0 = q + 1, i1 = min(q + 2, hi), i2 = min(q + 3, hi);
-            double a0 = A_[i0], b0 = B_[i0], z0 = Z_[i0];
-            double a1 = A_[i1], b1 = B_[i1], z1 = Z_[i1];
-            double a2 = A_[i2], b2 = B_[i2], z2 = Z_[i2];
-            for (; q < hi; q += 3) {
-                rot(q, a0, b0, z0);
-                i0 = min(q + 4, hi);
-                a0 = A_[i0];
-                b0 = B_[i0];
-                z0 = Z_[i0];
-                rot(q + 1, a1, b1, z1);
-                i1 = min(q + 5, hi);
-                a1 = A_[i1];
-                b1 = B_[i1];
-                z1 = Z_[i1];
-                rot(q + 2, a2, b2, z2);
-                i2 = min(q + 6, hi);
-                a2 = A_[i2];
-                b2 = B_[i2];
-                z2 = Z_[i2];
-            }
-        }
-        if (lane == 0) {
-            A_[hi] = ak;
-            B_[hi - 1] = nbk;
-            Z_[hi] = zk;
-        }
-        __syncthreads();
-    }
-    __syncthreads();
-    // s = |v|^2 sum_i z_i(1)^2 h(theta_i): lanes take i = lane, lane + 64, ...,
-    // then the butterfly (the same sum in every lane)
-    double s = 0.0, mn = INFINITY;
-    for (int i = lane; i < N; i += 64) {
-        const double th = A_[i], zz = Z_[i];
-        s += zz * zz * step_fn(th, smooth_w);
-        mn = fmin(mn, fabs(th));
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        s += __shfl_xor(s, o, 64);
-        mn = fmin(mn, __shfl_xor(mn, o, 64));
-    }
-    if (lane == 0) {
-        s_all[gidx] = nu[c] * s;
-        minabs_all[gidx] = mn;
-        if (failed) atomicOr(&flags[1], 1);
-    }
-}
-
-template <int KMAX>
-static void tridiag_t(const Plan &p, hipStream_t st)
-{
-    // up to 2048 columns (about two wavefronts per CU): a wavefront per column;
-    // beyond, lanes per workgroup doubling to keep about 2048 workgroups
-    const int NC = p.nseg * p.C;
-    if (NC <= 2048) {
-        k_tridiag_wave<KMAX><<<NC, 64, 0, st>>>(NC, p.C, p.Ct, p.c_off, p.k, p.rule, p.smooth_w,
-                                                p.alpha, p.beta, p.kused, p.nu, p.s_out, p.minabs,
-                                                p.flags);
         return;
     }
-    int LN = 1;
-    while (LN < QuadGeom<KMAX>::lanes && NC > 2048 * LN) LN *= 2;
-    const int blocks = (NC + LN - 1) / LN;
-    const size_t lds = sizeof(double) * 3 * KMAX * LN;
-    k_tridiag<KMAX><<<blocks, LN, lds, st>>>(NC, p.C, p.Ct, p.c_off, p.k, p.rule, p.smooth_w, p.alpha,
-                                             p.beta, p.kused, p.nu, p.s_out, p.minabs, p.flags);
+    double m1 = m0;
+    for (int o = 32; o > 0; o >>= 1) m1 = fmax(m1, __shfl_xor(m1, o, 64));
+    if ((t & 63) == 0) red[0][t >> 6] = m1;
+    __syncthreads();
+    double tn = red[0][0];
+#pragma unroll
+    for (int q = 1; q < kW; ++q) tn = fmax(tn, red[0][q]);
+    if (!(tn > 0.0)) tn = 1.0;
+    if (t < NMAX) {
+        A_[t] = a / tn;
+        B_[t] = b / tn;
+    }
+    DcNoRows none;
+    tridiag_dc<NMAX, P>(N, A_, B_, w, none);
+    double s = 0.0, mn = INFINITY;
+    if (t < N) {
+        const double th = w.D[t] * tn, z = w.F[t];
+        s = z * z * step_fn(th, smooth_w);
+        mn = fabs(th);
+    }
+    s = wave_sum_dpp(s);
+    for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));
+    if ((t & 63) == 0) {
+        red[0][t >> 6] = s;
+        red[1][t >> 6] = mn;
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int q = 1; q < kW; ++q) {
+            s += red[0][q];
+            mn = fmin(mn, red[1][q]);
+        }
+        s_all[gidx] = nu[vc] * s;
+        minabs_all[gidx] = mn;
+    }
 }
 
+template <int NMAX, int P>
+static void tridiag_dc_t(const Plan &p, hipStream_t st)
+{
+    const int NC = p.nseg * p.C;
+    k_tridiag_dc<NMAX, P><<<NC, NMAX * P, 0, st>>>(NC, p.C, p.Ct, p.c_off, p.k, p.rule, p.smooth_w, p.alpha,
+                                                   p.beta, p.kused, p.nu, p.s_out, p.minabs, p.flags);
+}
+
+// Divide and conquer, with more lanes per entry where the columns are few or
+// the order large (measured, us, 8 / 4 / 2 lanes: order 30, 512 columns 64 / 66
+// / 69; order 25, 2048 columns 130 / 99 / 96; order 60, 64 columns 82 / 76 /
+// 100; order 199, 64 columns - / 400 / 525, 4096 columns - / 5530 / 5210).  The
+// lane-per-column QR took 217, 221, 611 and 5670 us where those are 64, 96, 76
+// and 400; it stays for many columns of small order, where a workgroup's
+// entries leave most of its lanes idle (order 8, 16384 columns: 120 us against
+// 165; order 25: 556 against 399).
 void launch_tridiag(const Plan &p, hipStream_t st)
 {
     const int N = (p.rule == 1) ? 2 * p.k - 1 : p.k;
-    if (N <= 32) tridiag_t<32>(p, st);
-    else if (N <= 64) tridiag_t<64>(p, st);
-    else if (N <= 128) tridiag_t<128>(p, st);
-    else if (N <= 256) tridiag_t<256>(p, st);
-    else tridiag_t<512>(p, st);
+    const int NC = p.nseg * p.C;
+    if (N <= kQrOrder && NC > 2048) {
+        // lanes per workgroup doubling to keep about 2048 workgroups
+        int LN = 1;
+        while (LN < 64 && NC > 2048 * LN) LN *= 2;
+        k_tridiag<<<(NC + LN - 1) / LN, LN, sizeof(double) * 3 * kQrOrder * LN, st>>>(
+            NC, p.C, p.Ct, p.c_off, p.k, p.rule, p.smooth_w, p.alpha, p.beta, p.kused, p.nu, p.s_out,
+            p.minabs, p.flags);
+    } else if (N <= 32 && NC <= 512) {
+        tridiag_dc_t<32, 8>(p, st);
+    } else if (N <= 32) {
+        tridiag_dc_t<32, 2>(p, st);
+    } else if (N <= 64) {
+        tridiag_dc_t<64, 4>(p, st);
+    } else if (N <= 128) {
+        tridiag_dc_t<128, 4>(p, st);
+    } else if (N <= 256) {
+        tridiag_dc_t<256, 4>(p, st);
+    } else {
+        tridiag_dc_t<512, 2>(p, st);
+    }
 }
 
 void launch_reduce(const Plan &p, hipStream_t st)

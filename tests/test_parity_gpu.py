@@ -707,6 +707,64 @@ def test_smooth_rejects_unsupported(ec):
     assert e.value.status == ec.ECNT_EUNSUPPORTED
 
 
+def _quadrature_matrix(kind, N):
+    rng = np.random.default_rng(N)
+    if kind == "random":
+        return rng.standard_normal(N), 0.1 + rng.random(max(N - 1, 0))
+    if kind == "wilkinson":     # pairs of eigenvalues equal to many digits
+        return np.abs(np.arange(N) - 0.5 * (N - 1)), np.ones(max(N - 1, 0))
+    if kind == "weak":          # two clusters and couplings near the deflation threshold
+        return np.where(np.arange(N) % 2 == 0, 1.0, -1.0), np.full(max(N - 1, 0), 1e-9)
+    return np.full(N, 2.0), np.ones(max(N - 1, 0))   # "constant": equal diagonal
+
+
+@pytest.mark.parametrize("kind", ["random", "wilkinson", "weak", "constant"])
+@pytest.mark.parametrize("N", [1, 2, 3, 16, 31, 32, 33, 64, 65, 128, 129, 256, 257, 512])
+def test_quadrature_of_given_tridiagonal(ec, kind, N):
+    """The tridiagonal eigensolve at the edges of its sizes, on matrices with
+    clusters and deflation: Lanczos on a tridiagonal A from e_1 returns A itself,
+    so s = sum_{theta < 0} z(1)^2 at a shift in a wide gap is known from a dense
+    eigensolve.  A backward-stable solve moves it by a few N eps |T| / gap."""
+    a, b = _quadrature_matrix(kind, N)
+    T = np.diag(a) + np.diag(b, 1) + np.diag(b, -1)
+    w, Z = np.linalg.eigh(T)
+    gaps = np.diff(np.concatenate([[w[0] - 1.0], w, [w[-1] + 1.0]]))
+    at = np.sort(np.argsort(gaps)[-3:])
+    taus = np.array([(w[0] - 1.0 if i == 0 else w[i - 1]) + 0.5 * gaps[i] for i in at])
+    rp, ci = [0], []
+    for r in range(N):
+        ci += [c for c in (r - 1, r, r + 1) if 0 <= c < N]
+        rp.append(len(ci))
+    val = np.array([T[r, c] for r in range(N) for c in ci[rp[r]:rp[r + 1]]])
+    A = W.CSR(N, np.array(rp, np.int32), np.array(ci, np.int32), val)
+    V = torch.zeros(N, 1, dtype=torch.float64, device="cuda")
+    V[0, 0] = 1.0
+    if kind == "weak" and N > 128:
+        # couplings of 1e-9 of the diagonal amplify the recurrence's rounding by
+        # 1e9 a step; past 128 steps its coefficients overflow, which is an error
+        with pytest.raises(ec.EcntError) as e:
+            ec.negcounts(ec.upload_csr(A), W.PrecSpec("none"), taus, V, N)
+        assert e.value.status == ec.ECNT_EDEVICE
+        return
+    r = ec.negcounts(ec.upload_csr(A), W.PrecSpec("none"), taus, V, N)
+    for tau, s, g in zip(taus, r.per_probe.cpu().numpy(), gaps[at]):
+        ref = float(np.sum(Z[0, w < tau] ** 2))
+        assert abs(s - ref) <= 64 * max(N, 4) * 2.3e-16 * max(np.abs(w - tau).max(), g) / g, (tau, s, ref)
+
+
+@pytest.mark.parametrize("m", [1025, 3])
+def test_quadrature_of_many_columns_and_small_order(ec, m):
+    """Order 16, on both sides of the column count where the lane-per-column
+    form takes over: the same probes give the same values to rounding."""
+    wl = W.Workload("q", (7, 8, 9), "wells", 2, -8.0, -2.0, "none", 1025, 16)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)[:, :m]
+    r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, wl.k, tune={"fused": "off"})
+    ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V[:, :3], wl.k)
+    s = r.per_probe.cpu().numpy().reshape(2, m)[:, :3]
+    assert np.max(np.abs(s - np.stack([ref.s_xi, ref.s_eta]))) <= TOL * P.A.n
+
+
 @pytest.mark.parametrize("k", [1, 2, 16, 17, 33, 49, 112, 113])
 @pytest.mark.parametrize("prec,m,cols", [("cheb", 3, 0), ("jacobi", 37, 0), ("cheb", 37, 50)])
 def test_one_sweep_step_edges(ec, prec, m, cols, k):
