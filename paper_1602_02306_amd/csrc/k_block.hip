@@ -19,14 +19,17 @@
 // A[l%16][l/16] and B[l/16][l%16]; accumulator register v of lane l holds
 // D[4v + l/16][l%16].
 //
-// Quadrature (k_blk_quad): T_k (order 16 k_used, half-bandwidth 16) is reduced
-// to tridiagonal form by Householder bulge chasing, then diagonalized by
-// implicit QR sweeps with Wilkinson shifts; the first 16 rows of the
-// accumulated eigenvector matrix follow every transform, all in LDS.
+// Quadrature: T_k (order 16 k_used, half-bandwidth 16) is reduced to tridiagonal
+// form by Householder bulge chasing in one wavefront's LDS (k_blk_tridiag), and
+// that is diagonalized by divide and conquer (k_blk_dc, tridiag_dc.h); the first
+// 16 rows of the accumulated eigenvector matrix follow every transform.
 #include <float.h>
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "ecount_internal.h"
+#include "tridiag_dc.h"
 
 namespace ecnt {
 
@@ -241,34 +244,30 @@ __device__ __forceinline__ double mm16(const double *a, bool ta, const double *b
     return s;
 }
 
-// Upper Cholesky factor R (G = R^T R) and its inverse, by one thread.
-// Returns false if a pivot is not positive and finite.
-__device__ bool chol_inv16(const double *G, double *R, double *Ri)
+// Upper Cholesky factor R (G = R^T R, G overwritten) and its inverse, by the
+// workgroup, row by row (one thread took 90 us).  Returns false, in every
+// thread, if a pivot is not positive and finite.
+__device__ __forceinline__ bool chol_inv16(double *G, double *R, double *Ri, int t)
 {
-    for (int i = 0; i < 256; ++i) {
-        R[i] = 0.0;
-        Ri[i] = 0.0;
-    }
+    const int r = t >> 4, c = t & 15;
+    R[t] = 0.0;
+    Ri[t] = r == c ? 1.0 : 0.0;
     for (int j = 0; j < 16; ++j) {
-        double s = G[j * 16 + j];
-        for (int k = 0; k < j; ++k) s -= R[k * 16 + j] * R[k * 16 + j];
-        if (!(s > 0.0) || !isfinite(s)) return false;
+        __syncthreads();
+        const double s = G[j * 17];
+        if (!(s > 0.0) || !isfinite(s)) return false;   // the same s in every thread
         const double rjj = sqrt(s);
-        R[j * 16 + j] = rjj;
-        for (int c = j + 1; c < 16; ++c) {
-            double u = G[j * 16 + c];
-            for (int k = 0; k < j; ++k) u -= R[k * 16 + j] * R[k * 16 + c];
-            R[j * 16 + c] = u / rjj;
-        }
+        if (r == j && c >= j) R[t] = c == j ? rjj : G[t] / rjj;
+        __syncthreads();
+        if (r > j && c > j) G[t] -= R[j * 16 + r] * R[j * 16 + c];
     }
-    for (int j = 0; j < 16; ++j) {
-        Ri[j * 16 + j] = 1.0 / R[j * 16 + j];
-        for (int r = j - 1; r >= 0; --r) {
-            double u = 0.0;
-            for (int k = r + 1; k <= j; ++k) u += R[r * 16 + k] * Ri[k * 16 + j];
-            Ri[r * 16 + j] = -u / R[r * 16 + r];
-        }
+    for (int k = 15; k >= 0; --k) {
+        __syncthreads();
+        if (r == k) Ri[t] /= R[k * 17];
+        __syncthreads();
+        if (r < k) Ri[t] -= R[r * 16 + k] * Ri[k * 16 + c];
     }
+    __syncthreads();
     return true;
 }
 
@@ -324,7 +323,7 @@ __global__ __launch_bounds__(256) void k_blk_norm_fin(int mode, int step, int k,
                                                       int32_t *__restrict__ kused)
 {
     __shared__ double G[256], Sl[256], U[256], R[256], Ri[256];
-    __shared__ int ok_s;
+    __shared__ double mx[4];
     const int blk = blockIdx.x, t = threadIdx.x;
     const int i = step;
     const bool alive = mode >= 2 || act[blk] != 0;
@@ -339,23 +338,26 @@ __global__ __launch_bounds__(256) void k_blk_norm_fin(int mode, int step, int k,
         G[t] = g;
         __syncthreads();
     }
+    bool ok = chol_inv16(G, R, Ri, t) && alive;
+    double rmax = 0.0;
+    if (ok && mode == 1) {
+        // B_{i+1} = R2 R1 (diagonal = products of the diagonals)
+        double m = fabs(Ab[(size_t)blk * 256 + t]);
+        if (i > 1) m = fmax(m, fabs(Bb[((size_t)(i - 1) * nblk + blk) * 256 + t]));
+        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+        if ((t & 63) == 0) mx[t >> 6] = m;
+        __syncthreads();
+        rmax = fmax(fmax(rm[blk], fmax(mx[0], mx[1])), fmax(mx[2], mx[3]));
+        double mn = INFINITY;
+        for (int j = 0; j < 16; ++j)
+            mn = fmin(mn, R[j * 16 + j] * R1[(size_t)blk * 256 + j * 16 + j]);
+        if (mn <= 1e3 * DBL_EPSILON * rmax) ok = false;
+    }
+    const bool update_max = alive && (mode == 1 && rmax > 0.0);
+    __syncthreads();   // every read of rm is done
     if (t == 0) {
-        bool ok = alive && chol_inv16(G, R, Ri);
-        if (ok && mode == 1) {
-            // B_{i+1} = R2 R1 (diagonal = products of the diagonals)
-            double r = rm[blk];
-            for (int e = 0; e < 256; ++e) r = fmax(r, fabs(Ab[(size_t)blk * 256 + e]));
-            if (i > 1)
-                for (int e = 0; e < 256; ++e)
-                    r = fmax(r, fabs(Bb[((size_t)(i - 1) * nblk + blk) * 256 + e]));
-            rm[blk] = r;
-            double mn = INFINITY;
-            for (int j = 0; j < 16; ++j)
-                mn = fmin(mn, R[j * 16 + j] * R1[(size_t)blk * 256 + j * 16 + j]);
-            if (mn <= 1e3 * DBL_EPSILON * r) ok = false;
-        }
+        if (update_max) rm[blk] = rmax;
         if (mode == 2) rm[blk] = 0.0;
-        ok_s = ok ? 1 : 0;
         if (alive && !ok) {
             act[blk] = 0;
             for (int j = 0; j < 16; ++j) kused[c_off + blk * kBlk + j] = mode >= 2 ? 0 : i;
@@ -363,7 +365,6 @@ __global__ __launch_bounds__(256) void k_blk_norm_fin(int mode, int step, int k,
         if (mode >= 2 && ok) act[blk] = 1;
     }
     __syncthreads();
-    const bool ok = ok_s != 0;
     const int r = t >> 4, c = t & 15;
     if (mode == 2 || mode == 0) {
         // T = S_i R1^{-1} (mode 0) or R1^{-1}; keep R1
@@ -397,6 +398,7 @@ constexpr int kQN = kQMax + 18;
 // diagonals held: the half-bandwidth kBlk plus the fill that the chase leaves
 // behind (distance at most 2 kBlk - 2 from the diagonal)
 constexpr int kDiag = 2 * kBlk - 1;
+constexpr int kTriRows = 2 + kBlk;   // doubles per order handed from the chase to the eigensolve
 
 __device__ __forceinline__ int bidx(int r, int c)
 {
@@ -428,33 +430,22 @@ __device__ __forceinline__ int zidx(int r, int c)
 // [I 0]; only the first reflector of each sweep meets its nonzero columns
 // (they grow by one column per sweep), so it is kept as a sliding 16 x 16
 // window in registers, and each finished column is stored in the band slots
-// of its T column, which the chase no longer uses.  Then implicit QR sweeps
-// with Wilkinson shifts diagonalize the tridiagonal form, every rotation also
-// applied to Z, all in LDS.
-__global__ __launch_bounds__(64) void k_blk_quad(int nblk, int c_off, double smooth_w,
-                                                 const double *__restrict__ Ab,
-                                                 const double *__restrict__ Bb,
-                                                 const double *__restrict__ R0,
-                                                 const int32_t *__restrict__ kused,
-                                                 double *__restrict__ s_out,
-                                                 double *__restrict__ minabs,
-                                                 int32_t *__restrict__ flags)
+// of its T column, which the chase no longer uses.  Out, per block (stride
+// `ld`): the diagonal, the off-diagonal, and Z by columns of 16.
+__global__ __launch_bounds__(64) void k_blk_tridiag(int nblk, int c_off, int k,
+                                                    const double *__restrict__ Ab,
+                                                    const double *__restrict__ Bb,
+                                                    const int32_t *__restrict__ kused,
+                                                    double *__restrict__ tri)
 {
     __shared__ double Lb[kDiag * kQN];
-    __shared__ double F[256];
     __shared__ double xbuf[kBlk];     // the column that gives the next reflector
     __shared__ double dump[64];       // per-lane target of the writes a lane does not make
     __shared__ double zslot[1];       // 0.0: the source of the reads a lane does not make
     const int blk = blockIdx.x, lane = threadIdx.x;
     const int col0 = c_off + blk * kBlk;
     const int ku = kused[col0];
-    if (ku < 1) {
-        if (lane < kBlk) {
-            s_out[col0 + lane] = 0.0;
-            minabs[col0 + lane] = INFINITY;
-        }
-        return;
-    }
+    if (ku < 1) return;
     const int N = ku * kBlk;
     // T_k into band storage: A_i on the diagonal blocks, B_{i+1} (upper
     // triangular) in block (i, i-1); the fill diagonals start at zero
@@ -639,141 +630,141 @@ __global__ __launch_bounds__(64) void k_blk_quad(int nblk, int c_off, double smo
     }
     __syncthreads();
 
-    // ---- implicit QR sweeps with Wilkinson shifts on (diagonal 0, diagonal 1) ----
-    // every lane runs the scalar chain and rotates row lane mod 16 of Z
-    double *A_ = Lb;
-    double *B_ = Lb + kQN;
-    const int zrow = lane & 15;
-    double *Zr = Lb + zidx(zrow, 0);   // row zrow of Z (lanes 16.. repeat rows 0..15)
-    int hi = N - 1, iter = 0;
-    bool failed = false;
-    while (hi > 0) {
-        if (fabs(B_[hi - 1]) <= DBL_EPSILON * (fabs(A_[hi - 1]) + fabs(A_[hi])) ||
-            fabs(B_[hi - 1]) < DBL_MIN) {
-            __syncthreads();
-            if (lane == 0) B_[hi - 1] = 0.0;
-            __syncthreads();
-            --hi;
-            continue;
+    double *out = tri + (size_t)blk * kTriRows * kBlk * k;
+    for (int q = lane; q < N; q += 64) {
+        out[q] = Lb[q];
+        out[kBlk * k + q] = q + 1 < N ? Lb[kQN + q] : 0.0;
+    }
+    for (int e = lane; e < 16 * N; e += 64) out[2 * kBlk * k + e] = Lb[zidx(e & 15, e >> 4)];
+}
+
+// W (16 rows, by columns) times the vectors, a column per thread
+struct BlkRows {
+    double (*W)[kBlk];
+    double acc[kBlk];
+    __device__ void rotate(int a, int b, double c, double g)
+    {
+        for (int r = 0; r < kBlk; ++r) {
+            const double x = W[a][r], y = W[b][r];
+            W[a][r] = c * x + g * y;
+            W[b][r] = c * y - g * x;
         }
-        // the largest lo < hi with B_[lo-1] negligible (or 0), 64 candidates at a time
-        int lo = 0;
-        for (int base = hi - 1; base > 0; base -= 64) {
-            const int i = base - lane;
-            bool neg = false;
-            if (i >= 1) {
-                const double bl = fabs(B_[i - 1]);
-                neg = bl <= DBL_EPSILON * (fabs(A_[i - 1]) + fabs(A_[i])) || bl < DBL_MIN;
-            }
-            const unsigned long long m = __ballot(neg);
-            if (m) {
-                lo = base - (__ffsll((long long)m) - 1);
-                break;
-            }
+    }
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int r = 0; r < kBlk; ++r) acc[r] = 0.0;
+    }
+    __device__ __forceinline__ void copy(int i)
+    {
+#pragma unroll
+        for (int r = 0; r < kBlk; ++r) acc[r] = W[i][r];
+    }
+    __device__ __forceinline__ void add(int i, double u)
+    {
+#pragma unroll
+        for (int r = 0; r < kBlk; ++r) acc[r] = fma(u, W[i][r], acc[r]);
+    }
+    __device__ __forceinline__ void scale(double x)
+    {
+#pragma unroll
+        for (int r = 0; r < kBlk; ++r) acc[r] *= x;
+    }
+    __device__ __forceinline__ void store(int i)
+    {
+#pragma unroll
+        for (int r = 0; r < kBlk; ++r) W[i][r] = acc[r];
+    }
+};
+
+// Eigenvalues of the tridiagonal form and Z times its vectors, then
+// s_j = (R0^T Z h(Theta) Z^T R0)_jj; one workgroup of NMAX threads per block.
+// O(N^2) work a row in log2(N) parallel steps: QR sweeps by one wavefront took
+// 13 of the 16.6 ms at 16 blocks of order 320.
+template <int NMAX>
+__global__ __launch_bounds__(NMAX) void k_blk_dc(int nblk, int c_off, int k, double smooth_w,
+                                                 const double *__restrict__ tri,
+                                                 const double *__restrict__ R0,
+                                                 const int32_t *__restrict__ kused,
+                                                 double *__restrict__ s_out, double *__restrict__ minabs,
+                                                 int32_t *__restrict__ flags)
+{
+    constexpr int kW = NMAX / 64;
+    __shared__ DcLds<NMAX> w;
+    __shared__ double A_[NMAX], B_[NMAX], red[kBlk + 1][kW];
+    __shared__ double W[NMAX][kBlk];
+    const int blk = blockIdx.x, t = threadIdx.x;
+    const int col0 = c_off + blk * kBlk;
+    const int ku = kused[col0];
+    if (ku < 1) {
+        if (t < kBlk) {
+            s_out[col0 + t] = 0.0;
+            minabs[col0 + t] = INFINITY;
         }
-        if (++iter > 60 * N) {
-            failed = true;
-            break;
+        return;
+    }
+    const int N = ku * kBlk;
+    const double *in = tri + (size_t)blk * kTriRows * kBlk * k;
+    double a = 0.0, b = 0.0;
+    if (t < N) {
+        a = in[t];
+        b = in[kBlk * k + t];
+    }
+    double m = fmax(fabs(a), fabs(b));
+    if (__syncthreads_or(!(fabs(a) <= DBL_MAX) || !(fabs(b) <= DBL_MAX))) {
+        if (t < kBlk) {
+            s_out[col0 + t] = NAN;
+            minabs[col0 + t] = NAN;
         }
-        const double bb0 = B_[hi - 1];
-        const double dh = 0.5 * (A_[hi - 1] - A_[hi]);
-        const double den = dh + copysign(hypot(dh, bb0), dh);
-        const double mu = A_[hi] - (den != 0.0 ? bb0 * bb0 / den : 0.0);
-        double x = A_[lo] - mu, y = B_[lo];
-        if (lo > 0 && lane == 0) B_[lo - 1] = 0.0;   // the split found above (not read by the sweep)
-        // the values a rotation changes and the next one reads (A[q], B[q],
-        // row `zrow` of Z at q) are carried in registers; the ones it reads
-        // ahead (A[q+1], B[q+1], Z at q+1, not yet written in this sweep) come
-        // from three register sets by position mod 3, each reloaded three
-        // indices ahead once its rotation has used it.  The main loop runs
-        // three rotations with no condition inside (the first (hi - lo) mod 3
-        // rotations read their operands directly), so every load lands in the
-        // register that carries it and stays in flight for two rotations.
-        // Indices are clamped to hi: B[hi] is 0 (set when hi last moved down,
-        // or beyond the matrix), which is what a sweep's last rotation takes
-        // for B[q+1].
-        double ak = A_[lo], bk = B_[lo];
-        double zk = Zr[lo];
-        double nbk = bk;
-        auto rot = [&](int q, double ak1, double bk1, double z1) __attribute__((always_inline)) {
-            // (q2 = 0 only when x = y = 0: then r = sn = 0 as they stand)
-            const double q2 = x * x + y * y;
-            const bool nz = q2 > 0.0;
-            const double ir = rsqrt_pos(nz ? q2 : 1.0);
-            const double r = q2 * ir;
-            const double cs = nz ? x * ir : 1.0;
-            const double sn = y * ir;
-            const double na = cs * cs * ak + 2.0 * cs * sn * bk + sn * sn * ak1;
-            const double na1 = sn * sn * ak - 2.0 * cs * sn * bk + cs * cs * ak1;
-            nbk = cs * sn * (ak1 - ak) + (cs * cs - sn * sn) * bk;
-            // every lane writes: the scalar values are the same in all lanes,
-            // and lanes 16.. repeat the Z rows of lanes 0..15 with the same
-            // values; the first rotation of a sweep has no B to write (slot
-            // kQN - 1, past every B the sweeps read and before Z's first row)
-            B_[q > lo ? q - 1 : kQN - 1] = r;
-            A_[q] = na;
-            Zr[q] = cs * zk + sn * z1;
-            zk = -sn * zk + cs * z1;
-            ak = na1;
-            bk = cs * bk1;
-            x = nbk;
-            y = sn * bk1;
-        };
-        int q = lo;
-        for (const int q0 = lo + (hi - lo) % 3; q < q0; ++q) {
-            const int i = q + 1;
-            rot(q, A_[i], B_[i], Zr[i]);
-        }
-        if (q < hi) {
-            int i0 = q + 1, i1 = min(q + 2, hi), i2 = min(q + 3, hi);
-            double a0 = A_[i0], b0 = B_[i0], z0 = Zr[i0];
-            double a1 = A_[i1], b1 = B_[i1], z1 = Zr[i1];
-            double a2 = A_[i2], b2 = B_[i2], z2 = Zr[i2];
-            for (; q < hi; q += 3) {
-                rot(q, a0, b0, z0);
-                i0 = min(q + 4, hi);
-                a0 = A_[i0];
-                b0 = B_[i0];
-                z0 = Zr[i0];
-                rot(q + 1, a1, b1, z1);
-                i1 = min(q + 5, hi);
-                a1 = A_[i1];
-                b1 = B_[i1];
-                z1 = Zr[i1];
-                rot(q + 2, a2, b2, z2);
-                i2 = min(q + 6, hi);
-                a2 = A_[i2];
-                b2 = B_[i2];
-                z2 = Zr[i2];
-            }
-        }
-        if (lane == 0) {
-            A_[hi] = ak;
-            B_[hi - 1] = nbk;
-        }
-        Zr[hi] = zk;
-        __syncthreads();
+        if (t == 0) atomicOr(&flags[1], 1);
+        return;
+    }
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    if ((t & 63) == 0) red[0][t >> 6] = m;
+    B_[t] = b;
+    __syncthreads();
+    double tn = red[0][0];
+#pragma unroll
+    for (int q = 1; q < kW; ++q) tn = fmax(tn, red[0][q]);
+    if (!(tn > 0.0)) tn = 1.0;
+    // the signs of the off-diagonal into the vectors: T = S |T| S
+    if (t < N) {
+        int neg = 0;
+        for (int q = 0; q < t; ++q) neg += B_[q] < 0.0 ? 1 : 0;
+        const double sg = (neg & 1) ? -1.0 : 1.0;
+#pragma unroll
+        for (int r = 0; r < kBlk; ++r) W[t][r] = sg * in[2 * kBlk * k + (size_t)t * kBlk + r];
     }
     __syncthreads();
-    // F = Z h(Theta) Z^T, then S = R0^T F R0 (diagonal only)
-    for (int e = lane; e < 256; e += 64) {
-        const int a = e >> 4, b = e & 15;
-        double s = 0.0;
-        for (int q = 0; q < N; ++q) s += Lb[zidx(a, q)] * Lb[zidx(b, q)] * blk_step(A_[q], smooth_w);
-        F[e] = s;
+    A_[t] = a / tn;
+    B_[t] = fabs(b) / tn;
+    BlkRows rows;
+    rows.W = W;
+    tridiag_dc<NMAX, 1>(N, A_, B_, w, rows);
+    const double th = t < N ? w.D[t] * tn : INFINITY;
+    const double h = t < N ? blk_step(th, smooth_w) : 0.0;
+    double mn = fabs(th);
+    for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));
+    if ((t & 63) == 0) red[kBlk][t >> 6] = mn;
+    const double *R = R0 + (size_t)blk * 256;
+    for (int j = 0; j < kBlk; ++j) {
+        double y = 0.0;
+        if (t < N)
+            for (int r = 0; r <= j; ++r) y += R[r * 16 + j] * W[t][r];
+        const double v = wave_sum_dpp(h * y * y);
+        if ((t & 63) == 0) red[j][t >> 6] = v;
     }
     __syncthreads();
-    if (lane < kBlk) {
-        const double *R = R0 + (size_t)blk * 256;
-        double s = 0.0;
-        for (int a = 0; a <= lane; ++a)
-            for (int b = 0; b <= lane; ++b) s += R[a * 16 + lane] * F[a * 16 + b] * R[b * 16 + lane];
-        double mn = INFINITY;
-        for (int q = 0; q < N; ++q) mn = fmin(mn, fabs(A_[q]));
-        s_out[col0 + lane] = s;
-        minabs[col0 + lane] = mn;
+    if (t < kBlk) {
+        double sum = 0.0, lo = red[kBlk][0];
+#pragma unroll
+        for (int q = 0; q < kW; ++q) {
+            sum += red[t][q];
+            lo = fmin(lo, red[kBlk][q]);
+        }
+        s_out[col0 + t] = sum;
+        minabs[col0 + t] = lo;
     }
-    if (failed && lane == 0) atomicOr(&flags[1], 1);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -818,8 +809,19 @@ void launch_blk_norm_fin(const Plan &p, int mode, int step, hipStream_t st)
 
 void launch_blk_quad(const Plan &p, hipStream_t st)
 {
-    k_blk_quad<<<(unsigned)p.nblk, 64, 0, st>>>(p.nblk, p.c_off, p.smooth_w, p.bk_A, p.bk_B, p.bk_R0,
-                                                p.kused, p.s_out, p.minabs, p.flags);
+    // the tridiagonal forms go where the basis was, or (a handful of rows,
+    // hence few steps) where the partial sums were
+    const size_t need = (size_t)kTriRows * kBlk * p.k;
+    double *tri = (size_t)p.n * kBlk * (p.k + 1) >= need ? (double *)p.basis : p.bk_part;
+    k_blk_tridiag<<<(unsigned)p.nblk, 64, 0, st>>>(p.nblk, p.c_off, p.k, p.bk_A, p.bk_B, p.kused, tri);
+    auto dc = [&](auto n) {
+        k_blk_dc<decltype(n)::value><<<(unsigned)p.nblk, decltype(n)::value, 0, st>>>(
+            p.nblk, p.c_off, p.k, p.smooth_w, tri, p.bk_R0, p.kused, p.s_out, p.minabs, p.flags);
+    };
+    const int N = kBlk * p.k;
+    if (N <= 128) dc(std::integral_constant<int, 128>{});
+    else if (N <= 256) dc(std::integral_constant<int, 256>{});
+    else dc(std::integral_constant<int, 512>{});
 }
 
 }  // namespace ecnt

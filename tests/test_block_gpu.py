@@ -71,6 +71,19 @@ def test_block_parity(ec, name, kind):
     assert np.array_equal(r.k_used.cpu().numpy(), kused_ref(ref, 32))
 
 
+@pytest.mark.parametrize("k", [1, 2, 8, 9, 16, 17])
+def test_block_quadrature_orders(ec, k):
+    """Orders 16 k on both sides of each size of the divide-and-conquer
+    eigensolve (128, 256), and the smallest."""
+    dims = (9, 8, 7)
+    A = W.laplacian_csr(dims, W.gaussian_wells(dims, np.random.default_rng(3)))
+    prec = prec_of("cheb", dims)
+    V = W.rademacher(A.n, 16, 6)
+    r = run(ec, A, prec, -8.0, -2.0, V, k)
+    ref = oracle.block_count(A, prec, -8.0, -2.0, V, k)
+    check(r, ref, A.n)
+
+
 def test_block_column_waves_and_basis_chunks(ec):
     """k = 20 (three launches of at most 8 basis blocks per Gram-Schmidt pass)
     and column waves of one block each."""
