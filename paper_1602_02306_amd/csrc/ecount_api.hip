@@ -477,7 +477,9 @@ static void plan_onesweep(Plan &p, SegHost &sh)
 {
     p.onesweep = 0;
     p.part_rows = kPartRows;
-    if (p.vec_f32 || p.grad || p.arnoldi || p.block || p.k > kSweepMaxK) return;
+    if (p.vec_f32 || p.grad || p.block || p.k > kSweepMaxK) return;
+    // (the Arnoldi form keeps C w in the polynomial's third scratch block)
+    if (p.arnoldi && p.prec_kind != ECNT_PREC_CHEB_LAPLACIAN) return;
     // a smoothed count that the differentiated form also serves returns the
     // same estimate as its forward: the same form computes both
     if (p.smooth_w > 0.0 && p.rule == ECNT_RULE_GAUSS && p.prec_kind == ECNT_PREC_CHEB_LAPLACIAN &&
@@ -746,12 +748,41 @@ static void enqueue_wave_arnoldi(const Plan &p, const ecnt_csr *A, const void *p
         Timed t(F_SETUP, blk_b + (double)p.n * p.C * (p.vec_f32 ? 4 : 8) / p.S, st);
         launch_setup(p, probes, st);
     }
+    const size_t slot = slot_bytes(p);
+    char *basis = (char *)p.basis;
+    if (p.onesweep) {   // two reads of the basis per step (k_sweep.hip)
+        for (int i = 0; i < p.k; ++i) {
+            void *w = basis + (size_t)i * slot, *y = basis + (size_t)(i + 1) * slot, *z = p.tmp[2];
+            apply_A(p, A, w, nullptr, p.tmp[0], st);
+            apply_M(p, p.tmp[0], nullptr, p.tmp[1], y, z, z, false, st);   // slot i + 1 is scratch until the sweep
+            {
+                Timed t(F_FIN, 0.0, st);
+                launch_arn_sweep_fin(p, i, st);
+            }
+            {
+                Timed t(F_SWEEP, (i + 4) * blk_b, st);
+                launch_sweep(p, i, z, true, st);
+            }
+            {
+                Timed t(F_FIN, 0.0, st);
+                launch_arn_dots_fin(p, i, st);
+            }
+            const bool more = i + 1 < p.k;
+            Timed t(F_SWEEP, (i + (more ? 3 : 2)) * blk_b, st);
+            launch_sweep_plain(p, i + 1, more, st);
+        }
+        {
+            Timed t(F_FIN, 0.0, st);
+            launch_arn_sweep_fin(p, p.k, st);
+        }
+        Timed t(F_QUAD, 0.0, st);
+        launch_arn_quad(p, st);
+        return;
+    }
     {
         Timed t(F_FIN, 0.0, st);
         launch_setup_fin(p, st);
     }
-    const size_t slot = slot_bytes(p);
-    char *basis = (char *)p.basis;
     for (int j = 1; j <= p.k; ++j) {
         void *x = basis + (size_t)(j - 1) * slot;   // slot j-1 holds q_j (unnormalized)
         void *y = basis + (size_t)j * slot;         // slot j receives C q_j
@@ -924,7 +955,7 @@ static void enqueue_wave(const Plan &p, const ecnt_csr *A, const void *probes, h
                 launch_sweep_fin(p, i, st);
             }
             Timed t(F_SWEEP, (i + (i + 1 < p.k ? 4 : 3)) * blk_b, st);
-            launch_sweep(p, i, z, st);
+            launch_sweep(p, i, z, i + 1 < p.k, st);
         }
         {
             Timed t(F_FIN, 0.0, st);
@@ -1112,7 +1143,7 @@ static ecnt_status arnoldi_plan(Plan &p, SegHost &sh, int64_t n, int64_t m, cons
         return fail(ECNT_EUNSUPPORTED, "the Arnoldi estimator takes T = I or a Laplacian polynomial");
     if (o->rule != ECNT_RULE_GAUSS) return fail(ECNT_EUNSUPPORTED, "the Arnoldi estimator has no GA rule");
     if (o->smooth_w != 0.0) return fail(ECNT_EUNSUPPORTED, "the Arnoldi estimator uses the step h");
-    if (o->k > 64) return fail(ECNT_EUNSUPPORTED, "the Arnoldi estimator needs k <= 64");
+    if (o->k > kArnMaxK) return fail(ECNT_EUNSUPPORTED, "the Arnoldi estimator needs k <= %d", kArnMaxK);
     p.arnoldi = 1;
     return single_segment(p, sh, taus);
 }

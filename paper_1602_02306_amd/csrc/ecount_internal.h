@@ -31,6 +31,7 @@ constexpr int kMaxShifts = 64;
 constexpr int kMaxK = 512;
 constexpr int kSweepSlots = 16;    // basis slots per wavefront of the one-sweep Lanczos step
 constexpr int kSweepMaxK = 7 * kSweepSlots;   // seven wavefronts per workgroup
+constexpr int kArnMaxK = 64;        // Arnoldi steps
 constexpr int kBlk = 16;           // probe columns per block of the block-Lanczos form
 constexpr int kBlkMaxK = 32;       // block-Lanczos steps (T_k of order <= 512)
 constexpr int kBlkChunk = 32;      // basis blocks per block reorthogonalization launch
@@ -218,7 +219,12 @@ void launch_norm_fin(const Plan &p, int step, hipStream_t st);
 // the one-sweep step: u_i . z, the scalars of step i, the sweep (z = C u_i)
 void launch_dot_uz(const Plan &p, int i, const void *z, hipStream_t st);
 void launch_sweep_fin(const Plan &p, int i, hipStream_t st);
-void launch_sweep(const Plan &p, int i, const void *z, hipStream_t st);
+void launch_sweep(const Plan &p, int i, const void *z, bool store, hipStream_t st);
+// one Gram-Schmidt pass on slot i against slots 0..i-1 (cf) and the dots of the
+// result with them; Arnoldi's scalars before its two sweeps
+void launch_sweep_plain(const Plan &p, int i, bool store, hipStream_t st);
+void launch_arn_sweep_fin(const Plan &p, int i, hipStream_t st);
+void launch_arn_dots_fin(const Plan &p, int i, hipStream_t st);
 void launch_tridiag(const Plan &p, hipStream_t st);
 // the one-launch Lanczos form of small problems (k_small.hip)
 constexpr int kFusedMaxRows = 3072;   // rows of the largest segment

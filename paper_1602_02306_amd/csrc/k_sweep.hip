@@ -173,13 +173,122 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
     }
 }
 
+// ---- the same for Arnoldi (two classical Gram-Schmidt passes per step) ----
+// With w_i what the first pass left of C q_{i-1} and g' = Q^T w_i the second
+// pass's dots, per column:
+//   r = w_i - Q g',  h_{i, i-1} = |r|,  q_i = r / |r|
+//   C r = z - C Q g' = z - Q (H g') - g'_{i-1} r,   z = C w_i
+// so the sweep that finishes q_i also forms y = C q_i = C r / |r| and its dots
+// g = Q^T y, and a second sweep takes the first pass, w_{i+1} = y - Q g, and the
+// dots of the second, Q^T w_{i+1}: two reads of the basis per step, not four.
+// g' is of the order of rounding, so |r|^2 = |w_i|^2 - |g'|^2.
+
+// Before the first sweep of step i: column i - 1 of H, the breakdown test of
+// k_arn_norm_fin, and the sweep's coefficients.  i = k: only the column.
+__global__ __launch_bounds__(512) void k_arn_sweep_fin(int C, int nseg, int rows, int i, int k,
+                                                       double eps_vec,
+                                                       const int64_t *__restrict__ seg_chunk,
+                                                       const double *__restrict__ part,
+                                                       double *__restrict__ nu, double *__restrict__ sig,
+                                                       double *__restrict__ H, double *__restrict__ cf,
+                                                       double *__restrict__ ec, double *__restrict__ cu,
+                                                       double *__restrict__ cr,
+                                                       double *__restrict__ runmax,
+                                                       int32_t *__restrict__ active,
+                                                       int32_t *__restrict__ kused, int ku_ld, int ku_off)
+{
+    __shared__ double sh[kArnMaxK][64], red[2][8][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int NC = nseg * C;
+    const int vc = blockIdx.x * 64 + lane;
+    const bool valid = vc < NC;
+    const int v = valid ? vc : 0;
+    const int seg = v / C, c = v - seg * C;
+    const double *S = part + (size_t)seg_chunk[seg] * rows * C + c;
+    auto h = [&](int col, int row) -> double & { return H[((size_t)col * (k + 1) + row) * NC + v]; };
+    const double uu = S[0];
+    const bool was = i == 0 ? uu > 0.0 : active[v] != 0;
+    double hh = 0.0, hm = 0.0;
+    for (int l = w; l < i; l += 8) {
+        const double g = was ? S[(size_t)(1 + l) * C] * sig[(size_t)l * NC + v] : 0.0;
+        sh[l][lane] = g;
+        const double x = h(i - 1, l) + g;
+        if (valid) h(i - 1, l) = x;
+        hh += g * g;
+        hm = fmax(hm, fabs(x));
+    }
+    red[0][w][lane] = hh;
+    red[1][w][lane] = hm;
+    __syncthreads();
+    hh = hm = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        hh += red[0][q][lane];
+        hm = fmax(hm, red[1][q][lane]);
+    }
+    const double n2 = fmax(uu - hh, 0.0), b = sqrt(n2);
+    double rm = i > 0 ? fmax(runmax[v], hm) : 0.0;
+    const bool on = was && (i == 0 || b > 1e3 * eps_vec * rm);
+    const double sg = on ? 1.0 / b : 0.0;
+    if (on && i > 0) rm = fmax(rm, b);
+    const bool more = i < k;
+    if (more && valid) {
+        for (int l = w; l < i; l += 8) {
+            double t = 0.0;   // (H g')_l; column i - 1 was written by this thread
+            for (int m = l > 0 ? l - 1 : 0; m < i; ++m) t += h(m, l) * sh[m][lane];
+            const double sl = sig[(size_t)l * NC + v];
+            cf[(size_t)l * NC + v] = on ? sh[l][lane] * sl : 0.0;
+            ec[(size_t)l * NC + v] = on ? sg * t * sl : 0.0;
+        }
+    }
+    __syncthreads();   // every read of what is written below is done
+    if (!valid || w != 0) return;
+    if (i == 0) {
+        nu[v] = uu;
+        kused[(size_t)seg * ku_ld + ku_off + c] = on ? k : 0;
+    } else {
+        h(i - 1, i) = was ? b : 0.0;
+        if (was && !on) kused[(size_t)seg * ku_ld + ku_off + c] = i;
+    }
+    runmax[v] = rm;
+    active[v] = on ? 1 : 0;
+    sig[(size_t)i * NC + v] = sg;
+    if (more) {
+        cu[v] = 0.0;
+        cr[v] = i > 0 ? sg * sh[i - 1][lane] : 0.0;
+    }
+}
+
+// Before the second sweep of step i: g_l = q_l^T y, l = 0..i (row 1 + l).
+__global__ __launch_bounds__(64 * kFinWaves) void k_arn_dots_fin(int C, int nseg, int rows, int i, int k,
+                                                                 const int64_t *__restrict__ seg_chunk,
+                                                                 const double *__restrict__ part,
+                                                                 const double *__restrict__ sig,
+                                                                 const int32_t *__restrict__ active,
+                                                                 double *__restrict__ cf,
+                                                                 double *__restrict__ H)
+{
+    const int NC = nseg * C;
+    const int l = blockIdx.y;
+    const int vc = blockIdx.x * 64 + (threadIdx.x & 63);
+    const bool valid = vc < NC;
+    const int seg = valid ? vc / C : 0, c = valid ? vc - seg * C : 0;
+    const double s = block_chunk_sum(part, rows, C, 1 + l, c, seg_chunk[seg], seg_chunk[seg + 1], valid);
+    if (!valid || threadIdx.x >= 64) return;
+    const double sg = sig[(size_t)l * NC + vc];
+    const double g = active[vc] ? s * sg : 0.0;
+    cf[(size_t)l * NC + vc] = g * sg;
+    H[((size_t)i * (k + 1) + l) * NC + vc] = g;
+}
+
 // The sweep of step i.  A workgroup of W wavefronts takes one row chunk of one
 // 64-column tile; wavefront w owns slots w*NB.. (at most NB of the i), its
 // coefficients and running dots in registers.  Per R rows each wavefront adds
 // its slots' part of r and u_{i+1}; the parts meet in LDS (one barrier, two
 // buffers), every wavefront forms the same r and u_{i+1} and takes the dots
-// with its own slots, which are still in registers.
-template <int NB, int R>
+// with its own slots, which are still in registers.  PLAIN: r alone, and the
+// dots with r itself (a Gram-Schmidt pass and the next one's dots in one read).
+template <int NB, int R, bool PLAIN>
 __global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int nseg,
                                                const int64_t *__restrict__ seg_row,
                                                const int64_t *__restrict__ seg_chunk,
@@ -213,11 +322,12 @@ __global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int 
         const bool ok = l < nb;
         const int s = ok ? l0 + l : l0;
         co[l] = ok ? cf[(size_t)s * NC + vc] : 0.0;
-        eo[l] = ok ? ec[(size_t)s * NC + vc] : 0.0;
+        eo[l] = ok && !PLAIN ? ec[(size_t)s * NC + vc] : 0.0;
         so[l] = (size_t)s * ss;
         acc[l] = 0.0;
     }
-    const double wz = sig[(size_t)i * NC + vc], wu = cu[vc], wr = cr[vc];
+    const double wz = PLAIN ? 0.0 : sig[(size_t)i * NC + vc], wu = PLAIN ? 0.0 : cu[vc],
+                 wr = PLAIN ? 0.0 : cr[vc];
     double *U = basis + (size_t)i * ss, *UN = U + ss;
     double accr = 0.0, accu = 0.0;
     int buf = 0;
@@ -228,7 +338,7 @@ __global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int 
         for (int j = 0; j < R; ++j) {
             e[j] = (size_t)min(r + j, r1 - 1) * C + c;
             u[j] = U[e[j]];
-            z[j] = Z[e[j]];
+            z[j] = PLAIN ? 0.0 : Z[e[j]];
         }
 #pragma unroll
         for (int j = 0; j < R; ++j)
@@ -242,7 +352,7 @@ __global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int 
 #pragma unroll
             for (int l = 0; l < NB; ++l) {
                 a += co[l] * q[j][l];
-                b += eo[l] * q[j][l];
+                if (!PLAIN) b += eo[l] * q[j][l];
             }
             rr[j] = a;
             un[j] = b;
@@ -269,11 +379,14 @@ __global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int 
         for (int j = 0; j < R; ++j) {
             const bool live = r + j < r1;
             const double rv = u[j] - rr[j];
-            double uv = wz * z[j] - wu * u[j] - un[j];
-            uv -= wr * rv;
+            double uv = rv;
+            if (!PLAIN) {
+                uv = wz * z[j] - wu * u[j] - un[j];
+                uv -= wr * rv;
+            }
             if (w == 0 && live && colok) {
-                U[e[j]] = rv;
-                if (store_u) UN[e[j]] = uv;
+                if (!PLAIN || store_u) U[e[j]] = rv;
+                if (!PLAIN && store_u) UN[e[j]] = uv;
             }
             uv = live ? uv : 0.0;
 #pragma unroll
@@ -289,7 +402,7 @@ __global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int 
         if (l < nb) P[(size_t)(1 + l0 + l) * C] = acc[l];
     if (w == 0) {
         P[0] = accu;
-        P[(size_t)(1 + i) * C] = accr;
+        if (!PLAIN) P[(size_t)(1 + i) * C] = accr;
     }
 }
 
@@ -302,34 +415,55 @@ void launch_dot_uz(const Plan &p, int i, const void *z, hipStream_t st)
         (const double *)z, p.part_rows, i + 1, p.part);
 }
 
+// Chunk sums of the first `rows` rows.
+static void sweep_sum(const Plan &p, int rows, hipStream_t st)
+{
+    k_sweep_sum<<<dim3((p.nseg * p.C + 63) / 64, rows), 64 * kFinWaves, 0, st>>>(p.C, p.nseg, p.part_rows,
+                                                                               p.seg_chunk, p.part);
+}
+
 void launch_sweep_fin(const Plan &p, int i, hipStream_t st)
 {
-    const int NC = p.nseg * p.C;
-    const unsigned tiles = (NC + 63) / 64;
-    const int rows = i < p.k ? i + 2 : i + 1;
-    k_sweep_sum<<<dim3(tiles, rows), 64 * kFinWaves, 0, st>>>(p.C, p.nseg, p.part_rows, p.seg_chunk, p.part);
-    k_sweep_fin<<<tiles, 512, sizeof(double) * 64 * ((size_t)i + 16), st>>>(
+    sweep_sum(p, i < p.k ? i + 2 : i + 1, st);
+    k_sweep_fin<<<(p.nseg * p.C + 63) / 64, 512, sizeof(double) * 64 * ((size_t)i + 16), st>>>(
         p.C, p.nseg, p.part_rows, i, p.k, DBL_EPSILON, p.seg_chunk, p.part, p.nu, p.sig, p.alpha, p.beta,
         p.cf, p.ec, p.cu, p.cr, p.runmax, p.active, p.kused, p.Ct, p.c_off);
 }
 
-template <int NB>
-static void sweep_t(const Plan &p, int i, int W, const void *z, hipStream_t st)
+void launch_arn_sweep_fin(const Plan &p, int i, hipStream_t st)
 {
-    constexpr int R = NB > 8 ? 2 : 4;
-    k_sweep<NB, R><<<(unsigned)((int64_t)p.nchunk * p.nct), 64 * W, W > 1 ? sizeof(double2) * 2 * W * R * 64 : 0, st>>>(
-        p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (double *)p.basis, slot_elems(p), i,
-        (const double *)z, p.sig, p.cf, p.ec, p.cu, p.cr, i + 1 < p.k ? 1 : 0, p.part_rows, p.part);
+    sweep_sum(p, i + 1, st);
+    k_arn_sweep_fin<<<(p.nseg * p.C + 63) / 64, 512, 0, st>>>(
+        p.C, p.nseg, p.part_rows, i, p.k, DBL_EPSILON, p.seg_chunk, p.part, p.nu, p.sig, p.H, p.cf, p.ec, p.cu,
+        p.cr, p.runmax, p.active, p.kused, p.Ct, p.c_off);
 }
 
-void launch_sweep(const Plan &p, int i, const void *z, hipStream_t st)
+void launch_arn_dots_fin(const Plan &p, int i, hipStream_t st)
+{
+    const int NC = p.nseg * p.C;
+    k_arn_dots_fin<<<dim3((NC + 63) / 64, i + 1), 64 * kFinWaves, 0, st>>>(
+        p.C, p.nseg, p.part_rows, i, p.k, p.seg_chunk, p.part, p.sig, p.active, p.cf, p.H);
+}
+
+template <int NB, bool PLAIN>
+static void sweep_t(const Plan &p, int i, int W, const void *z, bool store, hipStream_t st)
+{
+    constexpr int R = NB > 8 ? 2 : 4;
+    k_sweep<NB, R, PLAIN><<<(unsigned)((int64_t)p.nchunk * p.nct), 64 * W,
+                            W > 1 ? sizeof(double2) * 2 * W * R * 64 : 0, st>>>(
+        p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (double *)p.basis, slot_elems(p), i,
+        (const double *)z, p.sig, p.cf, p.ec, p.cu, p.cr, store ? 1 : 0, p.part_rows, p.part);
+}
+
+template <bool PLAIN>
+static void sweep_nb(const Plan &p, int i, const void *z, bool store, hipStream_t st)
 {
     const int W = i > kSweepSlots ? (i + kSweepSlots - 1) / kSweepSlots : 1;
     const int nb = (i + W - 1) / W;
     switch (nb) {
-#define ECNT_CASE(N)              \
-    case N:                       \
-        sweep_t<N>(p, i, W, z, st); \
+#define ECNT_CASE(N)                               \
+    case N:                                        \
+        sweep_t<N, PLAIN>(p, i, W, z, store, st);  \
         break;
         ECNT_CASE(0) ECNT_CASE(1) ECNT_CASE(2) ECNT_CASE(3) ECNT_CASE(4) ECNT_CASE(5)
         ECNT_CASE(6) ECNT_CASE(7) ECNT_CASE(8) ECNT_CASE(9) ECNT_CASE(10) ECNT_CASE(11)
@@ -338,6 +472,16 @@ void launch_sweep(const Plan &p, int i, const void *z, hipStream_t st)
     default:
         break;
     }
+}
+
+void launch_sweep(const Plan &p, int i, const void *z, bool store, hipStream_t st)
+{
+    sweep_nb<false>(p, i, z, store, st);
+}
+
+void launch_sweep_plain(const Plan &p, int i, bool store, hipStream_t st)
+{
+    sweep_nb<true>(p, i, nullptr, store, st);
 }
 
 }  // namespace ecnt

@@ -77,6 +77,22 @@ def test_arnoldi_more_steps_and_waves(ec):
     check(r, ref, P.A.n, tol=1e-9)
 
 
+@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 33, 49, 63, 64])
+@pytest.mark.parametrize("m,cols", [(3, 0), (37, 50)])
+def test_arnoldi_two_sweep_step_edges(ec, m, cols, k):
+    """The two-sweep step where its split changes (one to four wavefronts of at
+    most 16 slots, in either sweep), with one and two column tiles, a ragged
+    last wave and 693 rows that no chunk divides; the tolerance is that of the
+    other cases with many steps."""
+    dims = (9, 7, 11)
+    A = W.laplacian_csr(dims, W.gaussian_wells(dims, np.random.default_rng(5)))
+    V = W.rademacher(A.n, m, 9)
+    T = t_spec("cheb", dims)
+    r = run(ec, A, T, -8.0, -2.0, V, k, max_cols=cols)
+    ref = oracle.count_arnoldi(A, T, -8.0, -2.0, V, k)
+    check(r, ref, A.n, tol=1e-9)
+
+
 def test_arnoldi_full_krylov_exact(ec):
     """k = n with Hadamard probes gives the exact inertia on the GPU as well."""
     dims = (4, 4, 4)
