@@ -104,37 +104,34 @@ __global__ void k_setup_fin(int C, int nseg, int k, const int64_t *__restrict__ 
 // q_i); GRAM = 2: slot_i is read as one more row.
 // Rows r0..r1 of the dots sweep; HASM: w = y - kappa q_{i-1} (otherwise w = y,
 // and q_{i-1} is not read).
-template <typename T, int NB, int VW, int GRAM, bool HASM>
-__device__ __forceinline__ void dots_rows(int C, int c0, int64_t r0, int64_t r1, const T *__restrict__ Y,
+template <typename T, int NB, int GRAM, bool HASM>
+__device__ __forceinline__ void dots_rows(int C, int c, int64_t r0, int64_t r1, const T *__restrict__ Y,
                                           const T *__restrict__ Qm, const T *__restrict__ Qi,
-                                          const T *__restrict__ Q0, size_t ss, const double (&kap)[VW],
-                                          double (&acc)[NB][VW], double (&gr)[GRAM > 0 ? NB : 1][VW])
+                                          const T *__restrict__ Q0, size_t ss, double kap,
+                                          double (&acc)[NB], double (&gr)[GRAM > 0 ? NB : 1])
 {
     for (int64_t r = r0; r < r1; ++r) {
-        const size_t e = (size_t)r * C + c0;
-        double y[VW], qm[VW], qi[VW], q[NB][VW];
-        vload<T, VW>(Y, e, y);
-        if (HASM) vload<T, VW>(Qm, e, qm);
-        if (GRAM == 2) vload<T, VW>(Qi, e, qi);
+        const size_t e = (size_t)r * C + c;
+        double y[1], qm[1], qi[1], q[NB][1];
+        vload<T, 1>(Y, e, y);
+        if (HASM) vload<T, 1>(Qm, e, qm);
+        if (GRAM == 2) vload<T, 1>(Qi, e, qi);
 #pragma unroll
-        for (int l = 0; l < NB; ++l) vload_nt<T, VW>(Q0 + (size_t)l * ss, e, q[l]);
+        for (int l = 0; l < NB; ++l) vload_nt<T, 1>(Q0 + (size_t)l * ss, e, q[l]);
         // keep all the row's loads in flight before the first use
         __builtin_amdgcn_sched_barrier(0);
+        const double w = HASM ? y[0] - kap * qm[0] : y[0];
 #pragma unroll
-        for (int v = 0; v < VW; ++v) {
-            const double w = HASM ? y[v] - kap[v] * qm[v] : y[v];
+        for (int l = 0; l < NB; ++l) acc[l] += q[l][0] * w;
+        if (GRAM > 0) {
+            const double qv = GRAM == 1 ? (double)q[NB - 1][0] : qi[0];
 #pragma unroll
-            for (int l = 0; l < NB; ++l) acc[l][v] += q[l][v] * w;
-            if (GRAM > 0) {
-                const double qv = GRAM == 1 ? (double)q[NB - 1][v] : qi[v];
-#pragma unroll
-                for (int l = 0; l < NB; ++l) gr[l][v] += q[l][v] * qv;
-            }
+            for (int l = 0; l < NB; ++l) gr[l] += q[l][0] * qv;
         }
     }
 }
 
-template <typename T, int NB, int VW, int GRAM>
+template <typename T, int NB, int GRAM>
 __global__ __launch_bounds__(64) void k_dots(int C, int nct, int64_t rpc, int nseg,
                                              const int64_t *__restrict__ seg_row,
                                              const int64_t *__restrict__ seg_chunk,
@@ -145,43 +142,30 @@ __global__ __launch_bounds__(64) void k_dots(int C, int nct, int64_t rpc, int ns
     const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
     const int ct = (int)(L % nct);
     const int64_t chunk = L / nct;
-    const int c0 = (ct * 64 + (int)threadIdx.x) * VW;
-    if (c0 >= C) return;
+    const int c = ct * 64 + (int)threadIdx.x;
+    if (c >= C) return;
     int seg;
     int64_t r0, r1;
     chunk_rows(seg_row, seg_chunk, nseg, rpc, chunk, seg, r0, r1);
-    const double *kappa = kappa_all + (size_t)seg * C;
-    double acc[NB][VW], gr[GRAM > 0 ? NB : 1][VW];
+    double acc[NB], gr[GRAM > 0 ? NB : 1];
 #pragma unroll
-    for (int l = 0; l < NB; ++l)
+    for (int l = 0; l < NB; ++l) acc[l] = 0.0;
 #pragma unroll
-        for (int v = 0; v < VW; ++v) acc[l][v] = 0.0;
-#pragma unroll
-    for (int l = 0; l < (GRAM > 0 ? NB : 1); ++l)
-#pragma unroll
-        for (int v = 0; v < VW; ++v) gr[l][v] = 0.0;
-    double kap[VW];
-#pragma unroll
-    for (int v = 0; v < VW; ++v) kap[v] = slot_m >= 0 ? kappa[c0 + v] : 0.0;
+    for (int l = 0; l < (GRAM > 0 ? NB : 1); ++l) gr[l] = 0.0;
+    const double kap = slot_m >= 0 ? kappa_all[(size_t)seg * C + c] : 0.0;
     const T *Y = basis + (size_t)slot_y * ss;
     const T *Qm = basis + (size_t)(slot_m >= 0 ? slot_m : 0) * ss;
     const T *Qi = basis + (size_t)(GRAM == 2 ? slot_i : 0) * ss;
     const T *Q0 = basis + (size_t)l0 * ss;
     if (slot_m >= 0)
-        dots_rows<T, NB, VW, GRAM, true>(C, c0, r0, r1, Y, Qm, Qi, Q0, ss, kap, acc, gr);
+        dots_rows<T, NB, GRAM, true>(C, c, r0, r1, Y, Qm, Qi, Q0, ss, kap, acc, gr);
     else
-        dots_rows<T, NB, VW, GRAM, false>(C, c0, r0, r1, Y, Qm, Qi, Q0, ss, kap, acc, gr);
+        dots_rows<T, NB, GRAM, false>(C, c, r0, r1, Y, Qm, Qi, Q0, ss, kap, acc, gr);
 #pragma unroll
-    for (int l = 0; l < NB; ++l)
-#pragma unroll
-        for (int v = 0; v < VW; ++v)
-            part[((size_t)chunk * kPartRows + l) * C + c0 + v] = acc[l][v];
+    for (int l = 0; l < NB; ++l) part[((size_t)chunk * kPartRows + l) * C + c] = acc[l];
     if (GRAM > 0) {
 #pragma unroll
-        for (int l = 0; l < NB; ++l)
-#pragma unroll
-            for (int v = 0; v < VW; ++v)
-                part[((size_t)chunk * kPartRows + NB + l) * C + c0 + v] = gr[l][v];
+        for (int l = 0; l < NB; ++l) part[((size_t)chunk * kPartRows + NB + l) * C + c] = gr[l];
     }
 }
 
@@ -368,24 +352,28 @@ void launch_setup_fin(const Plan &p, hipStream_t st)
                                                   p.Ct, p.c_off);
 }
 
-template <typename T, int NB, int VW>
+// One column per lane in both types.  Two per lane in FP32 (8-byte loads) read no
+// faster at 64^3 x 512 (42.0 ms of a count's dots against 41.8) and leave half the
+// lanes idle in an odd number of 64-column groups: 128^3 x 64 took 107.0 ms, one
+// per lane 82.7 (6.43 TB/s of the basis).
+template <typename T, int NB>
 static void dots_t(const Plan &p, int step, int l0, bool gram, hipStream_t st)
 {
-    const int nct = (p.C + 64 * VW - 1) / (64 * VW);
+    const int nct = (p.C + 63) / 64;
     const dim3 grid((unsigned)((int64_t)p.nchunk * nct));
     const int sm = (step >= 2 && !p.arnoldi) ? step - 2 : -1;
     if (gram && step - 1 == l0 + NB - 1)
-        k_dots<T, NB, VW, 1><<<grid, 64, 0, st>>>(p.C, nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk,
-                                                  (const T *)p.basis, slot_elems(p), step, l0, sm,
-                                                  p.kappa, step - 1, p.part);
+        k_dots<T, NB, 1><<<grid, 64, 0, st>>>(p.C, nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk,
+                                              (const T *)p.basis, slot_elems(p), step, l0, sm,
+                                              p.kappa, step - 1, p.part);
     else if (gram)
-        k_dots<T, NB, VW, 2><<<grid, 64, 0, st>>>(p.C, nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk,
-                                                  (const T *)p.basis, slot_elems(p), step, l0, sm,
-                                                  p.kappa, step - 1, p.part);
+        k_dots<T, NB, 2><<<grid, 64, 0, st>>>(p.C, nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk,
+                                              (const T *)p.basis, slot_elems(p), step, l0, sm,
+                                              p.kappa, step - 1, p.part);
     else
-        k_dots<T, NB, VW, 0><<<grid, 64, 0, st>>>(p.C, nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk,
-                                                  (const T *)p.basis, slot_elems(p), step, l0, sm,
-                                                  p.kappa, -1, p.part);
+        k_dots<T, NB, 0><<<grid, 64, 0, st>>>(p.C, nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk,
+                                              (const T *)p.basis, slot_elems(p), step, l0, sm,
+                                              p.kappa, -1, p.part);
 }
 
 template <typename T, int NB, int VW>
@@ -403,13 +391,13 @@ static void update_t(const Plan &p, int step, int l0, bool first, bool last, hip
     F(17) F(18) F(19) F(20) F(21) F(22) F(23) F(24) F(25) F(26) F(27) F(28) F(29) F(30)     \
     F(31) F(32)
 
-template <typename T, int VW>
+template <typename T>
 static void dots_nb(const Plan &p, int step, int l0, int nb, bool gram, hipStream_t st)
 {
     switch (nb) {
 #define ECNT_CASE(N) \
     case N:          \
-        dots_t<T, N, VW>(p, step, l0, gram, st); \
+        dots_t<T, N>(p, step, l0, gram, st); \
         break;
         ECNT_NB_CASES(ECNT_CASE)
 #undef ECNT_CASE
@@ -433,21 +421,10 @@ static void update_nb(const Plan &p, int step, int l0, int nb, bool first, bool 
     }
 }
 
-// Columns per lane of the FP32 dots: pairs (8-byte loads) when the wave width
-// is even; FP64 takes one column per lane (the NB accumulators per column
-// already fill the register budget).  Each launch derives its column tiles
-// from its own width; the partial sums are indexed by column.
-static inline int red_vw(const Plan &p) { return (p.vec_f32 && p.C % 2 == 0) ? 2 : 1; }
-
 void launch_dots(const Plan &p, int step, int l0, int nb, bool gram, hipStream_t st)
 {
-    if (p.vec_f32) {
-        // column pairs with the Gram column would spill beyond 24 basis vectors
-        if (red_vw(p) == 2 && !(gram && nb > 24)) dots_nb<float, 2>(p, step, l0, nb, gram, st);
-        else dots_nb<float, 1>(p, step, l0, nb, gram, st);
-    } else {
-        dots_nb<double, 1>(p, step, l0, nb, gram, st);
-    }
+    if (p.vec_f32) dots_nb<float>(p, step, l0, nb, gram, st);
+    else dots_nb<double>(p, step, l0, nb, gram, st);
 }
 
 void launch_dots_fin(const Plan &p, int step, int l0, int nb, bool gram, hipStream_t st)

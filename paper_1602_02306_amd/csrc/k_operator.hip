@@ -1058,6 +1058,17 @@ void launch_stencil_check(const Plan &p, const int32_t *row_ptr, const int32_t *
                                                       p.st_diag, p.st_coff, p.flags);
 }
 
+// Two columns per lane in FP32's grid sweeps: the width is even and fills pairs of
+// 64-column groups.  With an odd number of groups half the lanes of the last pair
+// idle through its walk: 128^3 x 64 columns, a count's quadratic sweeps 107 ms with
+// two columns per lane, 74 with one, A's sweeps 22.5 and 18.4.  At 64^3 x 512 pairs
+// are the faster, 37.5 to 39.7 ms of quadratic sweeps: a full pair costs 1.89 of one
+// group, a half-idle one 1.45, so one column per lane wins at every odd number.
+static bool lane_pairs(const Plan &p)
+{
+    return p.vec_f32 && p.C % 2 == 0 && ((p.C + 63) / 64) % 2 == 0;
+}
+
 template <typename T, int VW, int TX, int TY, int QX, int QY>
 static void stencil_a_t(const Plan &p, const void *x, const double *xs, void *y, hipStream_t st)
 {
@@ -1081,8 +1092,7 @@ static void stencil_a_shape(const Plan &p, const void *x, const double *xs, void
 
 void launch_stencil_a(const Plan &p, const void *x, const double *xs, void *y, hipStream_t st)
 {
-    // one column per lane (FP64) / two (FP32, when the width is even), as the plain sweep
-    if (p.vec_f32 && p.C % 2 == 0) stencil_a_shape<float, 2>(p, x, xs, y, st);
+    if (lane_pairs(p)) stencil_a_shape<float, 2>(p, x, xs, y, st);
     else if (p.vec_f32) stencil_a_shape<float, 1>(p, x, xs, y, st);
     else stencil_a_shape<double, 1>(p, x, xs, y, st);
 }
@@ -1271,8 +1281,8 @@ void launch_quad_sweep(const Plan &p, const void *X, const double *xs, double c1
     const double bo = 2.0 / w;
     const double bd1 = cb * bd, bo1 = cb * 2.0 / w;
     if (p.tx == 8) {   // workgroup-cooperative form on 8 x 8 line blocks, one column per lane
-        // (two in FP32 when the width is even: the planes then take what FP64's do)
-        if (p.vec_f32 && p.C % 2 == 0) {
+        // (two in FP32: the planes then take what FP64's do)
+        if (lane_pairs(p)) {
             if (Z) quad_sweep_wg_t<float, 2, true>(p, X, xs, c1, bd1, bo1, c2, bd, bo, Z, cz, out, st);
             else quad_sweep_wg_t<float, 2, false>(p, X, xs, c1, bd1, bo1, c2, bd, bo, Z, cz, out, st);
         } else if (p.vec_f32) {

@@ -377,6 +377,29 @@ def test_parity_launch_shapes(ec, tune):
     assert_parity(r, ref, k)
 
 
+@pytest.mark.parametrize("m", [1, 32, 33, 64, 65, 96, 97, 128])
+def test_fp32_columns_per_lane_edges(ec, m):
+    """FP32 count at the widths where the columns per lane change (2 m columns:
+    one, two, three and four groups of 64, full and ragged): the grid sweeps
+    against the oracle, and every width of the CSR sweep the same bits as the
+    default's, each column being summed in the same order."""
+    wl = W.WORKLOADS["c2_ragged"]
+    P = W.make_problem(wl)
+    V = W.rademacher(P.A.n, m, 23)
+    ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V, wl.k)
+    r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, wl.k, vec="f32")
+    s = r.per_probe.cpu().numpy()
+    s_ref = np.concatenate([ref.s_xi, ref.s_eta])
+    assert np.max(np.abs(s - s_ref)) <= 1e-4 * P.A.n
+    wl = W.WORKLOADS["c1"]
+    P = W.make_problem(wl)
+    V = W.rademacher(P.A.n, m, 29)
+    outs = [gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, 10, vec="f32", tune={"a_form": "csr", "csr_vw": vw})
+            for vw in (0, 1, 2, 4)]
+    for o in outs[1:]:
+        assert torch.equal(o.per_probe, outs[0].per_probe)
+
+
 def test_stencil_tile_shapes_bitwise(ec):
     """The plain stencil sweep computes each grid point the same way whatever
     the line block, so the tile shape alone changes no bit of the result."""
