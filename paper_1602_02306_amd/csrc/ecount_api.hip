@@ -213,10 +213,18 @@ size_t plan_layout(Plan &p, char *base)
 // Column geometry of a wave of width p.C.
 static void col_geometry(Plan &p)
 {
-    // columns per lane: 16-byte accesses where the column count allows it
-    if (p.vec_f32) p.vw = (p.C % 4 == 0) ? 4 : (p.C % 2 == 0 ? 2 : 1);
-    else p.vw = (p.C % 2 == 0) ? 2 : 1;
-    if (p.req_vw > 0 && p.req_vw <= p.vw && p.C % p.req_vw == 0) p.vw = p.req_vw;
+    // Columns per lane of the CSR sweep: what 16-byte accesses allow (and what a
+    // request is checked against), unless too many lanes of the last wavefront of a
+    // row would idle; a wavefront costs about the same however many of its lanes are busy.
+    // 300 x 300 Jacobi, the sweeps of a count, ms:
+    //   FP64, C = 40 / 64 / 96 / 128 / 192    one 2.2 / 2.2 / 4.1 / 4.5 / 6.9, two 3.3 / 3.2 / 3.3 / 3.8 / 7.3
+    //   FP32, C = 32 / 64 / 128 / 192 / 256  one 1.7 / 1.7 / 3.2 / 4.7 / 6.1,
+    //                                        two 3.3 / 3.4 / 3.4 / 6.5 / 6.6, four 5.5 / 5.5 / 5.6 / 5.7 / 5.8
+    const int groups = (p.C + 63) / 64;
+    const int most = p.vec_f32 && p.C % 4 == 0 ? 4 : (p.C % 2 == 0 ? 2 : 1);
+    const bool full = p.vec_f32 ? most == 4 && groups % 4 == 0 : groups != 1 && groups != 3;
+    p.vw = full ? most : 1;
+    if (p.req_vw > 0 && p.req_vw <= most && p.C % p.req_vw == 0) p.vw = p.req_vw;
     p.nct = (p.C + kColTile - 1) / kColTile;
 }
 
@@ -225,6 +233,8 @@ static void col_geometry(Plan &p)
 static void row_geometry(Plan &p, SegHost &sh)
 {
     // reductions: one wavefront per (row chunk, tile of 64 lanes); about 2048 of them
+    // (in FP32 counted as tiles of column pairs where the width is even: the chunks
+    // are the order in which the sums are taken)
     const int vwr = (p.vec_f32 && p.wave_cols % 2 == 0) ? 2 : 1;
     const int nctr = (p.wave_cols + 64 * vwr - 1) / (64 * vwr);
     const int waves = p.req_red_waves > 0 ? p.req_red_waves : 2048;
