@@ -570,6 +570,32 @@ static ecnt_status single_segment(Plan &p, SegHost &sh, const double *taus)
     return set_segments(p, sh, 1, &n, d, taus);
 }
 
+// alpha (k rows) and beta (k + 1 rows) of a wave's C columns into rows of Ct
+__global__ __launch_bounds__(256) void k_coef_out(int C, int Ct, int k, const double *__restrict__ alpha,
+                                                  const double *__restrict__ beta,
+                                                  double *__restrict__ alpha_out, double *__restrict__ beta_out)
+{
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= (size_t)(2 * k + 1) * C) return;
+    const int row = (int)(t / C), c = (int)(t % C);
+    if (row < k) {
+        if (alpha_out) alpha_out[(size_t)row * Ct + c] = alpha[(size_t)row * C + c];
+    } else if (beta_out) {
+        beta_out[(size_t)(row - k) * Ct + c] = beta[(size_t)(row - k) * C + c];
+    }
+}
+
+// the per-probe results into the caller's arrays
+__global__ __launch_bounds__(256) void k_probe_out(size_t n, const double *__restrict__ s,
+                                                   const int32_t *__restrict__ kused,
+                                                   double *__restrict__ s_out, int32_t *__restrict__ k_out)
+{
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= n) return;
+    if (s_out) s_out[t] = s[t];
+    if (k_out) k_out[t] = kused[t];
+}
+
 __global__ void k_init(int32_t *flags)
 {
     if (threadIdx.x < 4) flags[threadIdx.x] = 0;
@@ -704,14 +730,10 @@ static void enqueue(const Plan &p, const ecnt_csr *A, const void *probes, ecnt_i
         col_geometry(w);
         enqueue_wave(w, A, probes, st);
         // diagnostics of a single problem: alpha/beta of this wave into the caller's arrays
-        if (p.nseg == 1 && !p.arnoldi && !p.block && info && info->alpha)
-            (void)hipMemcpy2DAsync(info->alpha + c_off, sizeof(double) * p.Ct, w.alpha,
-                                   sizeof(double) * w.C, sizeof(double) * w.C, p.k,
-                                   hipMemcpyDeviceToDevice, st);
-        if (p.nseg == 1 && !p.arnoldi && !p.block && info && info->beta)
-            (void)hipMemcpy2DAsync(info->beta + c_off, sizeof(double) * p.Ct, w.beta,
-                                   sizeof(double) * w.C, sizeof(double) * w.C, p.k + 1,
-                                   hipMemcpyDeviceToDevice, st);
+        if (p.nseg == 1 && !p.arnoldi && !p.block && info && (info->alpha || info->beta))
+            k_coef_out<<<(unsigned)(((size_t)(2 * p.k + 1) * w.C + 255) / 256), 256, 0, st>>>(
+                w.C, p.Ct, p.k, w.alpha, w.beta, info->alpha ? info->alpha + c_off : nullptr,
+                info->beta ? info->beta + c_off : nullptr);
     }
     Timed t(F_QUAD, 0.0, st);
     launch_reduce(p, st);
@@ -1078,24 +1100,51 @@ static ecnt_status check_common(const ecnt_csr *A, const void *probes, const ecn
     return ECNT_OK;
 }
 
+// The segment tables lie one after the other from seg_row on.  Up to kPutMax
+// pieces of them go as kernel arguments, copied at the launch, so the host neither
+// waits for five small copies from pageable memory nor for the stream (with the
+// results in one copy and the details in two kernels, a 900-row, 80-column, k = 20
+// count takes 252 us, 296 before).  Larger tables (more than some 470 problems of
+// two shifts) are one copy, waited for.
+struct PutArgs {
+    uint64_t w[384];   // 3 KiB of the 4 that a launch's arguments may take
+};
+constexpr size_t kPutMax = 8;
+
+__global__ __launch_bounds__(384) void k_put(uint64_t *__restrict__ dst, int words, PutArgs a)
+{
+    if ((int)threadIdx.x < words) dst[threadIdx.x] = a.w[threadIdx.x];
+}
+
 static ecnt_status upload_tables(const Plan &p, const SegHost &sh, hipStream_t st)
 {
-    hipError_t e = hipMemcpyAsync(p.seg_row, sh.row.data(), sizeof(int64_t) * (p.nseg + 1),
-                                  hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p.seg_chunk, sh.chunk.data(), sizeof(int64_t) * (p.nseg + 1),
-                           hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p.seg_tile, sh.tile.data(), sizeof(int64_t) * (p.nseg + 1),
-                           hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p.seg_dims, sh.dims.data(), sizeof(int32_t) * 3 * p.nseg,
-                           hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p.seg_taus, sh.taus.data(), sizeof(double) * p.S * p.nseg,
-                           hipMemcpyHostToDevice, st);
-    // the host tables are locals of the caller: complete the copies before returning
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    char *const d0 = (char *)p.seg_row;
+    const size_t words = ((char *)p.seg_taus - d0) / 8 + (size_t)p.S * p.nseg;
+    std::vector<uint64_t> img(words, 0);
+    auto place = [&](const void *dev, const void *src, size_t bytes) {
+        memcpy((char *)img.data() + ((const char *)dev - d0), src, bytes);
+    };
+    place(p.seg_row, sh.row.data(), sizeof(int64_t) * (p.nseg + 1));
+    place(p.seg_chunk, sh.chunk.data(), sizeof(int64_t) * (p.nseg + 1));
+    place(p.seg_tile, sh.tile.data(), sizeof(int64_t) * (p.nseg + 1));
+    place(p.seg_dims, sh.dims.data(), sizeof(int32_t) * 3 * p.nseg);
+    place(p.seg_taus, sh.taus.data(), sizeof(double) * p.S * p.nseg);
+    constexpr size_t per = sizeof(PutArgs::w) / 8;
+    hipError_t e = hipSuccess;
+    if (words <= kPutMax * per) {
+        (void)hipGetLastError();
+        for (size_t o = 0; o < words; o += per) {
+            const size_t n = words - o < per ? words - o : per;
+            PutArgs a;
+            memcpy(a.w, img.data() + o, n * 8);
+            memset(a.w + n, 0, sizeof a.w - n * 8);
+            k_put<<<1, 384, 0, st>>>((uint64_t *)p.seg_row + o, (int)n, a);
+        }
+        e = hipGetLastError();
+    } else {
+        e = hipMemcpyAsync(d0, img.data(), words * 8, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);   // img is a local
+    }
     if (e != hipSuccess) return fail(ECNT_EDEVICE, "HIP error: %s", hipGetErrorString(e));
     return ECNT_OK;
 }
@@ -1104,18 +1153,29 @@ static ecnt_status upload_tables(const Plan &p, const SegHost &sh, hipStream_t s
 static ecnt_status finish(const Plan &p, hipStream_t st, double *res_host, ecnt_info *info)
 {
     int32_t flags[4] = {0, 0, 0, 0};
-    hipError_t e = hipMemcpyAsync(res_host, p.result, sizeof(double) * kResStride * p.nseg,
-                                  hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(flags, p.flags, sizeof flags, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && info) {
-        const size_t NCt = (size_t)p.nseg * p.Ct;
-        if (info->per_probe)
-            e = hipMemcpyAsync(info->per_probe, p.s_out, sizeof(double) * NCt, hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess && info->k_used)
-            e = hipMemcpyAsync(info->k_used, p.kused, sizeof(int32_t) * NCt, hipMemcpyDeviceToDevice, st);
+    const size_t NCt = (size_t)p.nseg * p.Ct;
+    hipError_t e = hipSuccess;
+    if (info && (info->per_probe || info->k_used)) {
+        (void)hipGetLastError();
+        k_probe_out<<<(unsigned)((NCt + 255) / 256), 256, 0, st>>>(NCt, p.s_out, p.kused, info->per_probe, info->k_used);
+        e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    // results, k_used and flags lie one after the other: one copy while that is small
+    const size_t res_bytes = sizeof(double) * kResStride * p.nseg;
+    const size_t span = (size_t)((char *)p.flags - (char *)p.result) + sizeof flags;
+    if (span <= (size_t)64 << 10) {
+        std::vector<char> img(span);
+        if (e == hipSuccess) e = hipMemcpyAsync(img.data(), p.result, span, hipMemcpyDeviceToHost, st);
+        // (also after an error: nothing may still write into img)
+        const hipError_t es = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = es;
+        memcpy(res_host, img.data(), res_bytes);
+        memcpy(flags, img.data() + span - sizeof flags, sizeof flags);
+    } else {
+        if (e == hipSuccess) e = hipMemcpyAsync(res_host, p.result, res_bytes, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(flags, p.flags, sizeof flags, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+    }
     if (e != hipSuccess) return fail(ECNT_EDEVICE, "HIP error: %s", hipGetErrorString(e));
     collect_profile(p.a_mode == 1 || (p.stencil_a && p.a_mode == 0 && flags[2] == 0));
     if (flags[0]) return fail(ECNT_ENOTHPD, "Jacobi preconditioner singular: a_rr == tau for some row");
@@ -1542,7 +1602,11 @@ ecnt_status ecnt_batch_prepare(const ecnt_csr *A, const ecnt_prec *T, const ecnt
     if (rc) return rc;
     char *base = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     plan_layout(p, base);
-    return upload_tables(p, sh, (hipStream_t)stream);
+    rc = upload_tables(p, sh, (hipStream_t)stream);
+    if (rc) return rc;
+    // complete on return: the launch sequence may go to another stream
+    const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
+    return e == hipSuccess ? ECNT_OK : fail(ECNT_EDEVICE, "HIP error: %s", hipGetErrorString(e));
 }
 
 // enqueue: kernel launches only (no host synchronization, no copies): may be

@@ -210,3 +210,14 @@ def test_batch_large_k(ec):
     print("batch k = 200", flush=True)
     r, _ = run_batch(ec, P, V, 200)
     check_against_oracle(P, r, V, 200)
+
+
+@pytest.mark.parametrize("nprob", [2, 70, 71, 500])
+def test_batch_segment_tables_of_all_sizes(ec, nprob):
+    """The tables of the problems go to the device as one piece, as two (more than
+    3 KiB: some 70 problems of two shifts), or as a copy (more than 24 KiB)."""
+    P = Problems([(4, 3, 3 + b % 3) for b in range(nprob)], nshift=2, seed=31)
+    rng = np.random.default_rng(32)
+    V = rng.choice([-1.0, 1.0], size=(int(P.off[-1]), 2))
+    r, _ = run_batch(ec, P, V, 5)
+    check_against_oracle(P, r, V, 5)
