@@ -526,8 +526,8 @@ def batch_accuracy(r):
             "method_exact": "LDL^T Sylvester inertia (nested dissection)"}
 
 
-CEILING_KIND = {"lz_update": "update_mix", "bw_update": "update_mix", "blk_update": "update_mix",
-                "lz_dots": "read", "bw_dots": "read", "blk_dots": "read"}
+CEILING_KIND = {"lz_sweep": "update_mix", "lz_update": "update_mix", "bw_update": "update_mix",
+                "blk_update": "update_mix", "lz_dots": "read", "bw_dots": "read", "blk_dots": "read"}
 
 
 def measure_ceilings(args):
@@ -579,11 +579,15 @@ def traffic_from_profiles(family: str, per_launch_algo: float, workload: str = "
 
 FAMILY_OF = [("k_blk_update<true>", "blk_normalize"), ("k_blk_update", "blk_update"),
              ("k_blk_dots_fin", "lz_finalize"), ("k_blk_norm_fin", "lz_finalize"),
-             ("k_blk_dots", "blk_dots"), ("k_blk_quad", "blk_quadrature"),
-             ("k_ldl_solve", "op_ldl_solve"), ("k_ldl_eapply", "op_ldl_elementwise"),
+             ("k_blk_dots", "blk_dots"), ("k_blk_tridiag", "blk_quadrature"),
+             ("k_blk_dc", "blk_quadrature"),
+             ("k_ldl_solve", "op_ldl_solve"), ("k_ldl_chain", "op_ldl_solve"), ("k_ldl_eapply", "op_ldl_elementwise"),
              ("k_ldl_permute", "op_ldl_elementwise"), ("k_ldl_band", "lz_setup"),
              ("k_ldl_eblocks", "lz_setup"),
              ("k_quad_sweep", "op_cheb_quad"), ("k_arn_quad", "quadrature"),
+             ("k_arn_sweep_fin", "lz_finalize"), ("k_arn_dots_fin", "lz_finalize"),
+             ("k_sweep_fin", "lz_finalize"), ("k_sweep_sum", "lz_finalize"), ("k_sweep", "lz_sweep"),
+             ("k_dot_uz", "lz_dots"), ("k_put", "copy"), ("k_coef_out", "copy"), ("k_probe_out", "copy"),
              ("k_arn_fin", "lz_finalize"), ("k_arn_norm_fin", "lz_finalize"),
              ("k_bdots_fin", "lz_finalize"),
              ("k_bnorm_fin", "lz_finalize"), ("k_rowsum", "lz_finalize"), ("k_vgrad", "bw_vgrad"),

@@ -110,7 +110,9 @@ typedef enum {
  *               block (non-zero there), 0 elsewhere
  *   nnz, bandwidth  entry count and max (i - j) over the entries
  * Each call first writes L and L^T into its workspace as bands of 256 values
- * per row (2 * 256 * 8 bytes per row and shift). */
+ * per row (2 * 256 * 8 bytes per row and shift).  With FP64 vectors and few
+ * columns the rows are solved in parts, which takes 1 MiB more per inner part
+ * and shift; a workspace that holds the bands only solves them whole. */
 typedef struct {
     const int32_t *perm;
     const int32_t *l_row_ptr;
@@ -191,7 +193,7 @@ typedef struct {
                            segment, at most 150 KiB), runs all k steps of every column
                            in one launch (one workgroup per column, its basis
                            column-contiguous in the workspace); otherwise, and with 1,
-                           the column-wave kernels (about five launches per step).  Both
+                           the column-wave kernels (several launches per step).  Both
                            compute the same recurrence; sums are in a different
                            order. */
 } ecnt_opts;

@@ -1,6 +1,8 @@
 // Lanczos recurrence with full reorthogonalization on a block of independent
 // probe columns (Algorithm 1; Section 3.2, the probe loop of Algorithm 2 run
-// data-parallel over columns).
+// data-parallel over columns).  The two-read step: FP32 vectors, k above
+// kSweepMaxK, the differentiated form and the smoothed counts that it also
+// serves; k_sweep.hip has the one-read step of the others.
 //
 // Step i of Algorithm 1, per column c (q_l = sig_{l-1} * slot_{l-1}):
 //   y      = C q_i                                (operator kernels, into slot i)
