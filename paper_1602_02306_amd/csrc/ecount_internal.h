@@ -29,8 +29,9 @@ constexpr int kBasisChunk = 32;    // basis vectors per reorthogonalization laun
 constexpr int kCUs = 256;           // compute units of an MI355X
 constexpr int kMaxShifts = 64;
 constexpr int kMaxK = 512;
-constexpr int kSweepSlots = 16;    // basis slots per wavefront of the one-sweep Lanczos step
-constexpr int kSweepMaxK = 7 * kSweepSlots;   // seven wavefronts per workgroup
+constexpr int kSweepWaves = 4;     // most wavefronts of a workgroup of the one-sweep Lanczos step
+constexpr int kSweepSlots = 28;    // most basis slots of each of them
+constexpr int kSweepMaxK = kSweepWaves * kSweepSlots;
 constexpr int kArnMaxK = 64;        // Arnoldi steps
 constexpr int kBlk = 16;           // probe columns per block of the block-Lanczos form
 constexpr int kBlkMaxK = 32;       // block-Lanczos steps (T_k of order <= 512)

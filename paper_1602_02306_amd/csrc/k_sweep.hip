@@ -21,9 +21,9 @@
 // q_{i-1} before C q_i enters anything.
 //
 // Bound: HBM.  Step i reads i + 2 block vectors and writes 2, against 2i + 3
-// read and 1 written for dots and update.  64^3 x 512 columns, k = 30: 119 ms
-// (5.0 TB/s) and 11 ms for u.z, against 109 ms of updates (5.2 TB/s) and 81 ms
-// of dots (6.6 TB/s); 32^3 x 64, k = 100: 19.5 ms against 33.1.
+// read and 1 written for dots and update.  64^3 x 512 columns, k = 30: 116 ms
+// (5.1 TB/s) and 11 ms for u.z, against 109 ms of updates (5.2 TB/s) and 81 ms
+// of dots (6.6 TB/s); 32^3 x 64, k = 100: 18.5 ms against 33.1.
 //
 // Slots: 0..k-1 hold r_0.. (unnormalized, scales sig as in k_lanczos.hip);
 // u_i lies in slot i until its sweep overwrites it with r_i; slot k holds z.
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * kFinWaves) void k_arn_dots_fin(int C, int nseg
 // with its own slots, which are still in registers.  PLAIN: r alone, and the
 // dots with r itself (a Gram-Schmidt pass and the next one's dots in one read).
 template <int NB, int R, bool PLAIN>
-__global__ __launch_bounds__(448) void k_sweep(int C, int nct, int64_t rpc, int nseg,
+__global__ __launch_bounds__(64 * kSweepWaves) void k_sweep(int C, int nct, int64_t rpc, int nseg,
                                                const int64_t *__restrict__ seg_row,
                                                const int64_t *__restrict__ seg_chunk,
                                                double *__restrict__ basis, size_t ss, int i,
@@ -448,7 +448,7 @@ void launch_arn_dots_fin(const Plan &p, int i, hipStream_t st)
 template <int NB, bool PLAIN>
 static void sweep_t(const Plan &p, int i, int W, const void *z, bool store, hipStream_t st)
 {
-    constexpr int R = NB > 8 ? 2 : 4;
+    constexpr int R = NB > 20 ? 1 : (NB > 8 ? 2 : 4);
     k_sweep<NB, R, PLAIN><<<(unsigned)((int64_t)p.nchunk * p.nct), 64 * W,
                             W > 1 ? sizeof(double2) * 2 * W * R * 64 : 0, st>>>(
         p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (double *)p.basis, slot_elems(p), i,
@@ -458,6 +458,11 @@ static void sweep_t(const Plan &p, int i, int W, const void *z, bool store, hipS
 template <bool PLAIN>
 static void sweep_nb(const Plan &p, int i, const void *z, bool store, hipStream_t st)
 {
+    // As few wavefronts as hold the slots: with one there is no exchange, and the rows
+    // of a step of R are fewer as the slots are more (28 slots, one row: 254
+    // registers).  At most 16 slots and seven wavefronts took, against 28 and four:
+    // 64^3 x 512, k = 30 119.6 ms of sweeps, 116.3; 32^3 x 64, k = 100 19.7, 18.5;
+    // Arnoldi 40^3 x 128, k = 30 14.3, 13.8; 24 and 30 slots are no faster.
     const int W = i > kSweepSlots ? (i + kSweepSlots - 1) / kSweepSlots : 1;
     const int nb = (i + W - 1) / W;
     switch (nb) {
@@ -467,7 +472,9 @@ static void sweep_nb(const Plan &p, int i, const void *z, bool store, hipStream_
         break;
         ECNT_CASE(0) ECNT_CASE(1) ECNT_CASE(2) ECNT_CASE(3) ECNT_CASE(4) ECNT_CASE(5)
         ECNT_CASE(6) ECNT_CASE(7) ECNT_CASE(8) ECNT_CASE(9) ECNT_CASE(10) ECNT_CASE(11)
-        ECNT_CASE(12) ECNT_CASE(13) ECNT_CASE(14) ECNT_CASE(15) ECNT_CASE(16)
+        ECNT_CASE(12) ECNT_CASE(13) ECNT_CASE(14) ECNT_CASE(15) ECNT_CASE(16) ECNT_CASE(17)
+        ECNT_CASE(18) ECNT_CASE(19) ECNT_CASE(20) ECNT_CASE(21) ECNT_CASE(22) ECNT_CASE(23)
+        ECNT_CASE(24) ECNT_CASE(25) ECNT_CASE(26) ECNT_CASE(27) ECNT_CASE(28)
 #undef ECNT_CASE
     default:
         break;

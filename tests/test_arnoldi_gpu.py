@@ -80,8 +80,8 @@ def test_arnoldi_more_steps_and_waves(ec):
 @pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 33, 49, 63, 64])
 @pytest.mark.parametrize("m,cols", [(3, 0), (37, 50)])
 def test_arnoldi_two_sweep_step_edges(ec, m, cols, k):
-    """The two-sweep step where its split changes (one to four wavefronts of at
-    most 16 slots, in either sweep), with one and two column tiles, a ragged
+    """The two-sweep step where its split changes (one to three wavefronts of at
+    most 28 slots, in either sweep), with one and two column tiles, a ragged
     last wave and 693 rows that no chunk divides; the tolerance is that of the
     other cases with many steps."""
     dims = (9, 7, 11)

@@ -792,7 +792,7 @@ def test_quadrature_of_many_columns_and_small_order(ec, m):
 @pytest.mark.parametrize("prec,m,cols", [("cheb", 3, 0), ("jacobi", 37, 0), ("cheb", 37, 50)])
 def test_one_sweep_step_edges(ec, prec, m, cols, k):
     """The one-sweep Lanczos step against the oracle where its split changes:
-    one to seven wavefronts of at most 16 slots, a wavefront with fewer slots
+    one to four wavefronts of at most 28 slots, a wavefront with fewer slots
     than the others, one and two column tiles (the last one ragged), column
     waves, and k = 113, which the two-read form takes.  n = 693: rows that no
     chunk divides.  s_j is within the oracle's rounding times the conditioning
@@ -802,6 +802,18 @@ def test_one_sweep_step_edges(ec, prec, m, cols, k):
     P = W.make_problem(wl)
     V = W.make_probes(wl)
     r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, k, tune={"fused": "off"}, max_cols=cols)
+    ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V, k)
+    assert_parity(r, ref, k if k <= 33 else None, probe_scale="nu")
+
+
+@pytest.mark.parametrize("k", [9, 20, 21, 28, 29, 56, 57, 84, 85])
+def test_one_sweep_rows_and_slots_edges(ec, k):
+    """As above at the sizes where the rows a wavefront takes at a time change
+    (four, two, one, at 8 and 20 slots) and where a wavefront is added (28 each)."""
+    wl = W.Workload("e", (9, 7, 11), "wells", 5, -8.0, -2.0, "cheb", 37, k)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)
+    r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, k, tune={"fused": "off"})
     ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V, k)
     assert_parity(r, ref, k if k <= 33 else None, probe_scale="nu")
 
