@@ -586,7 +586,7 @@ FAMILY_OF = [("k_blk_update<true>", "blk_normalize"), ("k_blk_update", "blk_upda
              ("k_ldl_eblocks", "lz_setup"),
              ("k_quad_sweep", "op_cheb_quad"), ("k_arn_quad", "quadrature"),
              ("k_arn_sweep_fin", "lz_finalize"), ("k_arn_dots_fin", "lz_finalize"),
-             ("k_sweep_fin", "lz_finalize"), ("k_sweep_sum", "lz_finalize"), ("k_sweep", "lz_sweep"),
+             ("k_sweep_fin", "lz_finalize"), ("k_sweep_sum", "lz_finalize"), ("k_uz_scale", "lz_finalize"), ("k_sweep", "lz_sweep"),
              ("k_dot_uz", "lz_dots"), ("k_put", "copy"), ("k_coef_out", "copy"), ("k_probe_out", "copy"),
              ("k_arn_fin", "lz_finalize"), ("k_arn_norm_fin", "lz_finalize"),
              ("k_bdots_fin", "lz_finalize"),

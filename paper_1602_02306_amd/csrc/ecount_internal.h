@@ -97,7 +97,7 @@ struct Plan {
     double *alpha = nullptr;   // k * C
     double *beta = nullptr;    // (k+1) * C
     double *cf = nullptr;      // (k+1) * NC   (update coefficients of the basis slots)
-    double *kappa = nullptr;   // C                 (beta_i * sig_{i-2})
+    double *kappa = nullptr;   // C                 (beta_i * sig_{i-2}; one-sweep step: the scale of u.z)
     double *runmax = nullptr;  // C
     double *nu = nullptr;      // C
     // ---- one-sweep Lanczos step (k_sweep.hip) ----

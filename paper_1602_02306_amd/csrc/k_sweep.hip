@@ -9,7 +9,7 @@
 // z = C u_i, per column (indices from 0, beta_i couples q_{i-1} and q_i):
 //   r      = u_i - Q h,          beta_i = |r|,  q_i = r / beta_i
 //   C r    = z - C Q h = z - h_{i-1} u_i - Q t,    t = T h
-//   alpha^ = r^T C r / beta_i^2
+//   alpha^ = r^T C r / beta_i^2   (u.z summed times a power of two, k_uz_scale)
 //   u_{i+1} = C r / beta_i - alpha^ q_i - beta_i q_{i-1}
 // where C Q h follows from the recurrence the basis satisfies (T the Lanczos
 // matrix so far, its last column completed by u_i itself).  h is of the order
@@ -36,12 +36,30 @@ namespace ecnt {
 
 // Rows of the partial sums of a chunk: 0 u.u, 1 + l slot_l.u (l < i), i + 1 u.z
 
-// part[chunk][row][c] = sum over the chunk's rows of U * Z
+// scale[vc]: a power of two near 1 / |u| for the sums u.z.  u and z = C u
+// are of the order of |C| and |C|^2 from step 1 on, so u.z would leave the range of
+// a double at |C| = 2^340 already, where |u|^2 does at 2^511.  Taken from the chunk
+// sums of |u|^2 (row 0) before the first two sums, the second for all later steps.
+__global__ __launch_bounds__(64 * kFinWaves) void k_uz_scale(int C, int nseg, int rows,
+                                                             const int64_t *__restrict__ seg_chunk,
+                                                             const double *__restrict__ part,
+                                                             double *__restrict__ scale)
+{
+    const int vc = blockIdx.x * 64 + (threadIdx.x & 63);
+    const bool valid = vc < nseg * C;
+    const int seg = valid ? vc / C : 0, c = valid ? vc - seg * C : 0;
+    const double uu = block_chunk_sum(part, rows, C, 0, c, seg_chunk[seg], seg_chunk[seg + 1], valid);
+    if (!valid || threadIdx.x >= 64) return;
+    scale[vc] = uu > 0.0 && uu <= DBL_MAX ? ldexp(1.0, -(ilogb(uu) / 2)) : 1.0;
+}
+
+// part[chunk][row][c] = scale * sum over the chunk's rows of U * Z
 __global__ __launch_bounds__(256) void k_dot_uz(int C, int nct, int64_t rpc, int nseg,
                                                 const int64_t *__restrict__ seg_row,
                                                 const int64_t *__restrict__ seg_chunk,
                                                 const double *__restrict__ U,
-                                                const double *__restrict__ Z, int rows, int row,
+                                                const double *__restrict__ Z,
+                                                const double *__restrict__ scale, int rows, int row,
                                                 double *__restrict__ part)
 {
     __shared__ double red[4][64];
@@ -55,9 +73,10 @@ __global__ __launch_bounds__(256) void k_dot_uz(int C, int nct, int64_t rpc, int
     const int64_t r1 = min(seg_row[seg + 1], r0 + rpc);
     double a = 0.0;
     if (c < C) {
+        const double sc = scale[(size_t)seg * C + c];
         for (int64_t r = r0 + wv; r < r1; r += 4) {
             const size_t e = (size_t)r * C + c;
-            a += U[e] * Z[e];
+            a += (U[e] * sc) * Z[e];
         }
     }
     red[wv][lane] = a;
@@ -86,6 +105,7 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
                                                    double eps_vec,
                                                    const int64_t *__restrict__ seg_chunk,
                                                    const double *__restrict__ part,
+                                                   const double *__restrict__ scale,
                                                    double *__restrict__ nu, double *__restrict__ sig,
                                                    double *__restrict__ alpha,
                                                    double *__restrict__ beta,
@@ -115,10 +135,11 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
         if (l >= 1) t += at(beta, l) * h(l - 1);
         return t;
     };
+    const double sc = scale[v];   // of the sums u.z and h.t
     double hh = 0.0, ht = 0.0;
     for (int l = w; l < i; l += 8) {
         hh += h(l) * h(l);
-        ht += h(l) * tl(l);
+        ht += (sc * h(l)) * tl(l);
     }
     double *red = sh + (size_t)i * 64;
     red[w * 64 + lane] = hh;
@@ -143,7 +164,7 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
     }
     const double sg = on ? 1.0 / b : 0.0;
     const bool more = i < k;
-    const double ah = (on && more) ? (S[(size_t)(i + 1) * C] - ht - 2.0 * hl * uu) / n2 : 0.0;
+    const double ah = (on && more) ? (S[(size_t)(i + 1) * C] - ht - 2.0 * (sc * hl) * uu) / (sc * n2) : 0.0;
     if (more && valid) {
         for (int l = w; l < i; l += 8) {
             const double sl = at(sig, l);
@@ -410,9 +431,12 @@ __global__ __launch_bounds__(64 * kSweepWaves) void k_sweep(int C, int nct, int6
 
 void launch_dot_uz(const Plan &p, int i, const void *z, hipStream_t st)
 {
+    if (i < 2)
+        k_uz_scale<<<(p.nseg * p.C + 63) / 64, 64 * kFinWaves, 0, st>>>(p.C, p.nseg, p.part_rows, p.seg_chunk,
+                                                                        p.part, p.kappa);
     k_dot_uz<<<(unsigned)((int64_t)p.nchunk * p.nct), 256, 0, st>>>(
         p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (const double *)p.basis + (size_t)i * slot_elems(p),
-        (const double *)z, p.part_rows, i + 1, p.part);
+        (const double *)z, p.kappa, p.part_rows, i + 1, p.part);
 }
 
 // Chunk sums of the first `rows` rows.
@@ -426,7 +450,7 @@ void launch_sweep_fin(const Plan &p, int i, hipStream_t st)
 {
     sweep_sum(p, i < p.k ? i + 2 : i + 1, st);
     k_sweep_fin<<<(p.nseg * p.C + 63) / 64, 512, sizeof(double) * 64 * ((size_t)i + 16), st>>>(
-        p.C, p.nseg, p.part_rows, i, p.k, DBL_EPSILON, p.seg_chunk, p.part, p.nu, p.sig, p.alpha, p.beta,
+        p.C, p.nseg, p.part_rows, i, p.k, DBL_EPSILON, p.seg_chunk, p.part, p.kappa, p.nu, p.sig, p.alpha, p.beta,
         p.cf, p.ec, p.cu, p.cr, p.runmax, p.active, p.kused, p.Ct, p.c_off);
 }
 

@@ -941,3 +941,20 @@ def test_fused_form_lds_limit(ec, side, fused):
     assert (prof["lz_dots"]["launches"] > 0) == (not fused)
     ref = oracle.count(A, prec, 0.5, 1.5, V, 24)
     assert_parity(r, ref, 24)
+
+
+@pytest.mark.parametrize("ea,ev", [(340, 0), (420, 0), (-340, 0), (-420, 0), (100, 470), (-100, -470)])
+def test_one_sweep_step_far_from_unit_scale(ec, ea, ev):
+    """A and the endpoints times 2^ea, the probes times 2^ev: every quantity of
+    the recurrence scales by a power of two, so the counts are those of the
+    unscaled call times 4^ev as long as |C|^2 and |v|^2 lie in the range of a
+    double, and alpha is its alpha times 2^ea."""
+    wl = W.Workload("e", (9, 7, 11), "wells", 5, 2.0, 6.0, "none", 5, 20)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)
+    A = W.CSR(P.A.n, P.A.row_ptr, P.A.col_idx, P.A.val * 2.0 ** ea)
+    print("case scale", ea, ev, flush=True)
+    a = gpu_count(ec, A, P.prec, wl.xi * 2.0 ** ea, wl.eta * 2.0 ** ea, V * 2.0 ** ev, wl.k, tune={"fused": "off"})
+    b = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, wl.k, tune={"fused": "off"})
+    assert float((a.per_probe / 4.0 ** ev - b.per_probe).abs().max()) <= TOL * float(b.per_probe.abs().max())
+    assert float((a.alpha / 2.0 ** ea - b.alpha).abs().max()) <= 1e-8 * float(b.alpha.abs().max())
