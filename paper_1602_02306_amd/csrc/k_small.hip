@@ -7,7 +7,7 @@
 //   g_l    = q_l^T w,  p_l = q_l^T q_i,  l = 1..i
 //   alpha_i = g_i;  c_l = g_l - alpha_i (p_l - [l = i])
 //   w     <- w - sum_l c_l q_l
-//   beta_{i+1} = |w|,  q_{i+1} = w / beta_{i+1}
+//   beta_{i+1} = |w|,  q_{i+1} = w / beta_{i+1}   (w <- w - Q Q^T w once more where |w| is small)
 // with C = M (A - tau I) M, M = I or the Jacobi scaling |diag(A) - tau I|^{-1/2}
 // (Section 5, the diagonal preconditioner), and the same breakdown rule
 // (beta_{i+1} <= 1e3 eps max(|alpha_l|, beta_l)).  A small count is latency
@@ -30,6 +30,11 @@ constexpr int kSmallThreads = 512;
 constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kLPer = (kFusedMaxK + kSmallWaves - 1) / kSmallWaves;   // basis vectors per wavefront
 static_assert(kLPer % 2 == 0, "the dots reduce two basis vectors at a time");
+// One pass leaves q_{i+1} orthogonal to about eps rm / beta_{i+1} (rm the largest
+// |alpha_l|, beta_l), and the next step multiplies what it finds by rm / beta
+// again: with several beta below sqrt(eps) rm in a row the basis is lost.  Below
+// kAgain rm, far above that, the pass is made twice; ordinary steps make one.
+constexpr double kAgain = 1e-6;
 }
 
 // sum over the workgroup, wavefronts in order; every thread gets the value
@@ -184,10 +189,28 @@ __global__ __launch_bounds__(kSmallThreads) void k_lanczos_fused(
                 ws[rl] = w;
                 ss += w * w;
             }
-            const double b = sqrt(group_sum(ss, red));
-            if (t == 0) beta[(size_t)i * NC + vc] = b;
+            double b = sqrt(group_sum(ss, red));
             rm = fmax(rm, fabs(al));
             if (i > 1) rm = fmax(rm, bprev);
+            if (b < kAgain * rm && b > 1e3 * eps * rm) {   // the pass once more
+                for (int l = wv; l < i; l += kSmallWaves) {
+                    const double *Ql = Q + (size_t)l * ns;
+                    double h = 0.0;
+                    for (int rl = lane; rl < ns; rl += 64) h += Ql[rl] * ws[rl];
+                    h = wave_sum_dpp(h);
+                    if (lane == 0) cf[l] = h;
+                }
+                __syncthreads();
+                ss = 0.0;
+                for (int rl = t; rl < ns; rl += kSmallThreads) {
+                    double w = ws[rl];
+                    for (int l = 0; l < i; ++l) w -= cf[l] * Q[(size_t)l * ns + rl];
+                    ws[rl] = w;
+                    ss += w * w;
+                }
+                b = sqrt(group_sum(ss, red));
+            }
+            if (t == 0) beta[(size_t)i * NC + vc] = b;
             if (b <= 1e3 * eps * rm) {   // breakdown: the column stops at k_used = i
                 ku = i;
                 break;

@@ -958,3 +958,43 @@ def test_one_sweep_step_far_from_unit_scale(ec, ea, ev):
     b = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, wl.k, tune={"fused": "off"})
     assert float((a.per_probe / 4.0 ** ev - b.per_probe).abs().max()) <= TOL * float(b.per_probe.abs().max())
     assert float((a.alpha / 2.0 ** ea - b.alpha).abs().max()) <= 1e-8 * float(b.alpha.abs().max())
+
+
+def weak_chain(N, b=1e-9):
+    """A dense symmetric matrix and a start vector whose Lanczos coefficients are
+    alpha = 1, -1, 1, ... and couplings of about b: (A, v, alpha)."""
+    a = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)
+    T = np.diag(a) + np.diag(np.full(N - 1, b), 1) + np.diag(np.full(N - 1, b), -1)
+    G = np.linalg.qr(np.random.default_rng(N).standard_normal((N, N)))[0]
+    D = G @ T @ G.T
+    D = 0.5 * (D + D.T)
+    A = W.CSR(N, np.arange(0, N * N + 1, N, dtype=np.int32), np.tile(np.arange(N, dtype=np.int32), N), D.ravel())
+    return A, G[:, :1].copy(), a
+
+
+def check_weak_chain(r, a, xi):
+    """Rounding turns every q_i by about N eps / b = 1e-5 within its +-1 cluster's
+    complement, which moves alpha by its square; a lost basis moves it by 2 and
+    more from the first steps on.  v lies in the positive cluster to 1e-9.  (A
+    column may stop early: the rounding that the couplings amplify can leave a
+    remainder below the breakdown bound as the space runs out.)"""
+    al = r.alpha.cpu().numpy()
+    ku = int(r.k_used[0])
+    assert ku >= len(a) - 8
+    assert np.max(np.abs(al[:ku, 0] + xi - a[:ku])) <= 1e-6
+    assert np.max(np.abs(r.per_probe.cpu().numpy() - [0.0, 1.0])) <= 1e-8
+
+
+@pytest.mark.parametrize("N", [8, 16, 33, 64])
+def test_fused_form_keeps_the_basis_under_weak_couplings(ec, N):
+    """Couplings of 1e-9 of the norm, step after step, in the one-launch form: one
+    Gram-Schmidt pass a step loses the basis by step 16."""
+    A, v, a = weak_chain(N)
+    xi, eta = -2.0, 1.5
+    print("case weak fused", N, flush=True)
+    ec.profile_enable(True)
+    r = gpu_count(ec, A, W.PrecSpec("none"), xi, eta, v, N)
+    prof = ec.profile_read()
+    ec.profile_enable(False)
+    assert prof["lz_fused"]["launches"] == 1
+    check_weak_chain(r, a, xi)
