@@ -29,9 +29,10 @@ constexpr int kBasisChunk = 32;    // basis vectors per reorthogonalization laun
 constexpr int kCUs = 256;           // compute units of an MI355X
 constexpr int kMaxShifts = 64;
 constexpr int kMaxK = 512;
-constexpr int kSweepWaves = 4;     // most wavefronts of a workgroup of the one-sweep Lanczos step
+constexpr int kSweepWaves = 5;     // most wavefronts of a workgroup of the one-sweep Lanczos step
 constexpr int kSweepSlots = 28;    // most basis slots of each of them
-constexpr int kSweepMaxK = kSweepWaves * kSweepSlots;
+constexpr int kSweepMaxK = 128;    // (k_sweep_fin holds 512 bytes of LDS per step)
+static_assert(kSweepMaxK <= kSweepWaves * kSweepSlots);
 constexpr int kArnMaxK = 64;        // Arnoldi steps
 constexpr int kBlk = 16;           // probe columns per block of the block-Lanczos form
 constexpr int kBlkMaxK = 32;       // block-Lanczos steps (T_k of order <= 512)

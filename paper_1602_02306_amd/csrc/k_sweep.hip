@@ -309,8 +309,8 @@ __global__ __launch_bounds__(64 * kFinWaves) void k_arn_dots_fin(int C, int nseg
 // buffers), every wavefront forms the same r and u_{i+1} and takes the dots
 // with its own slots, which are still in registers.  PLAIN: r alone, and the
 // dots with r itself (a Gram-Schmidt pass and the next one's dots in one read).
-template <int NB, int R, bool PLAIN>
-__global__ __launch_bounds__(64 * kSweepWaves) void k_sweep(int C, int nct, int64_t rpc, int nseg,
+template <int NB, int R, bool PLAIN, int WMAX>
+__global__ __launch_bounds__(64 * WMAX) void k_sweep(int C, int nct, int64_t rpc, int nseg,
                                                const int64_t *__restrict__ seg_row,
                                                const int64_t *__restrict__ seg_chunk,
                                                double *__restrict__ basis, size_t ss, int i,
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(64 * kSweepWaves) void k_sweep(int C, int nct, int6
                                                const double *__restrict__ cr, int store_u, int rows,
                                                double *__restrict__ part)
 {
-    extern __shared__ double2 xch[];   // [2][W][R][64]
+    extern __shared__ double2 xch[];   // [2][W][R][64], W <= WMAX
     constexpr int NA = NB > 0 ? NB : 1;
     const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
     const int ct = (int)(L % nct);
@@ -449,7 +449,10 @@ static void sweep_sum(const Plan &p, int rows, hipStream_t st)
 void launch_sweep_fin(const Plan &p, int i, hipStream_t st)
 {
     sweep_sum(p, i < p.k ? i + 2 : i + 1, st);
-    k_sweep_fin<<<(p.nseg * p.C + 63) / 64, 512, sizeof(double) * 64 * ((size_t)i + 16), st>>>(
+    const size_t lds = sizeof(double) * 64 * ((size_t)i + 16);
+    if (lds > (size_t)64 << 10)   // more than the default of dynamic LDS (not a stream operation)
+        (void)hipFuncSetAttribute((const void *)k_sweep_fin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    k_sweep_fin<<<(p.nseg * p.C + 63) / 64, 512, lds, st>>>(
         p.C, p.nseg, p.part_rows, i, p.k, DBL_EPSILON, p.seg_chunk, p.part, p.kappa, p.nu, p.sig, p.alpha, p.beta,
         p.cf, p.ec, p.cu, p.cr, p.runmax, p.active, p.kused, p.Ct, p.c_off);
 }
@@ -469,11 +472,11 @@ void launch_arn_dots_fin(const Plan &p, int i, hipStream_t st)
         p.C, p.nseg, p.part_rows, i, p.k, p.seg_chunk, p.part, p.sig, p.active, p.cf, p.H);
 }
 
-template <int NB, bool PLAIN>
+template <int NB, bool PLAIN, int WMAX = 4>
 static void sweep_t(const Plan &p, int i, int W, const void *z, bool store, hipStream_t st)
 {
     constexpr int R = NB > 20 ? 1 : (NB > 8 ? 2 : 4);
-    k_sweep<NB, R, PLAIN><<<(unsigned)((int64_t)p.nchunk * p.nct), 64 * W,
+    k_sweep<NB, R, PLAIN, WMAX><<<(unsigned)((int64_t)p.nchunk * p.nct), 64 * W,
                             W > 1 ? sizeof(double2) * 2 * W * R * 64 : 0, st>>>(
         p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (double *)p.basis, slot_elems(p), i,
         (const double *)z, p.sig, p.cf, p.ec, p.cu, p.cr, store ? 1 : 0, p.part_rows, p.part);
@@ -489,6 +492,18 @@ static void sweep_nb(const Plan &p, int i, const void *z, bool store, hipStream_
     // Arnoldi 40^3 x 128, k = 30 14.3, 13.8; 24 and 30 slots are no faster.
     const int W = i > kSweepSlots ? (i + kSweepSlots - 1) / kSweepSlots : 1;
     const int nb = (i + W - 1) / W;
+    if constexpr (!PLAIN) {
+        if (W > 4) {   // 113 to 127 slots: 23 to 26 in each of five wavefronts (at most 256 registers)
+            switch (nb) {
+#define ECNT_CASE(N)                                 \
+    case N:                                          \
+        sweep_t<N, false, 5>(p, i, W, z, store, st); \
+        return;
+                ECNT_CASE(23) ECNT_CASE(24) ECNT_CASE(25) ECNT_CASE(26)
+#undef ECNT_CASE
+            }
+        }
+    }
     switch (nb) {
 #define ECNT_CASE(N)                               \
     case N:                                        \

@@ -998,3 +998,31 @@ def test_fused_form_keeps_the_basis_under_weak_couplings(ec, N):
     ec.profile_enable(False)
     assert prof["lz_fused"]["launches"] == 1
     check_weak_chain(r, a, xi)
+
+
+@pytest.mark.parametrize("k", [112, 113, 120, 128])
+def test_one_sweep_step_keeps_the_basis_under_weak_couplings(ec, k):
+    """Couplings of 1e-9 of the norm up to the most steps of the one-sweep form
+    (four wavefronts up to 112 slots, five from there on)."""
+    A, v, a = weak_chain(144)
+    xi, eta = -2.0, 1.5
+    print("case weak one-sweep", k, flush=True)
+    ec.profile_enable(True)
+    r = gpu_count(ec, A, W.PrecSpec("none"), xi, eta, v, k)
+    prof = ec.profile_read()
+    ec.profile_enable(False)
+    assert prof["lz_sweep"]["launches"] == k
+    check_weak_chain(r, a[:k], xi)
+
+
+@pytest.mark.parametrize("rule", ["gauss", "ga"])
+@pytest.mark.parametrize("k", [114, 117, 121, 126, 127, 128, 129])
+def test_one_sweep_step_five_wavefronts(ec, k, rule):
+    """The one-sweep step of 113 to 127 slots (23 to 26 in a wavefront, the last
+    one with fewer) and the first order past it, as the smaller orders are tested."""
+    wl = W.Workload("e", (9, 7, 11), "wells", 5, -8.0, -2.0, "cheb", 37, k)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)
+    r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, k, rule=rule)
+    ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V, k, rule=rule)
+    assert_parity(r, ref, None, probe_scale="nu")
