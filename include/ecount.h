@@ -53,7 +53,11 @@ typedef int32_t ecnt_status;
 #define ECNT_EINVAL (-1)       /* invalid argument (null pointer, bad size, xi >= eta, ...) */
 #define ECNT_ENOTHPD (-2)      /* preconditioner not HPD (Jacobi pivot a_rr == tau)       */
 #define ECNT_EWORKSPACE (-3)   /* workspace missing or smaller than ecnt_workspace_bytes() */
-#define ECNT_EDEVICE (-4)      /* HIP runtime error, or the tridiagonal solver diverged   */
+#define ECNT_EDEVICE (-4)      /* HIP runtime error, the tridiagonal solver diverged, or
+                                  the Lanczos basis lost its orthogonality: FP64 with
+                                  k > 128, gradients and the smoothed counts they serve,
+                                  on operators whose beta stays below about 1e-7 of the
+                                  norm (the other FP64 forms keep the basis) */
 #define ECNT_EUNSUPPORTED (-5) /* valid request outside what the library supports        */
 
 typedef enum { ECNT_F64 = 0, ECNT_F32 = 1 } ecnt_dtype;

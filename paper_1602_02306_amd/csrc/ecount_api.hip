@@ -1179,6 +1179,9 @@ static ecnt_status finish(const Plan &p, hipStream_t st, double *res_host, ecnt_
     if (e != hipSuccess) return fail(ECNT_EDEVICE, "HIP error: %s", hipGetErrorString(e));
     collect_profile(p.a_mode == 1 || (p.stencil_a && p.a_mode == 0 && flags[2] == 0));
     if (flags[0]) return fail(ECNT_ENOTHPD, "Jacobi preconditioner singular: a_rr == tau for some row");
+    if (flags[1] & 2)
+        return fail(ECNT_EDEVICE, "the Lanczos basis lost its orthogonality (beta below about 1e-7 of the norm, "
+                                  "step after step; plain FP64 counts of k <= %d keep it)", kSweepMaxK);
     if (flags[1]) return fail(ECNT_EDEVICE, "tridiagonal eigensolver did not converge");
     return ECNT_OK;
 }

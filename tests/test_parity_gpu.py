@@ -1026,3 +1026,44 @@ def test_one_sweep_step_five_wavefronts(ec, k, rule):
     r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, k, rule=rule)
     ref = oracle.count(P.A, P.prec, wl.xi, wl.eta, V, k, rule=rule)
     assert_parity(r, ref, None, probe_scale="nu")
+
+
+@pytest.mark.parametrize("form,k", [("count", 129), ("count", 150), ("smooth", 32), ("smooth", 16), ("grad", 32),
+                                    ("batch", 130)])
+def test_lost_basis_is_reported(ec, form, k):
+    """The forms that make one Gram-Schmidt pass a step lose the basis under
+    couplings of 1e-9 of the norm (alpha off by 2 and far more): an error, not
+    those numbers.  Moderate couplings (1e-5) are answered as ever."""
+    N = 160
+    for b in (1e-9, 1e-5):
+        A, v, a = weak_chain(N, b)
+        Ad, Vd = ec.upload_csr(A), torch.from_numpy(v).cuda()
+        M1 = W.PrecSpec("cheb", (N, 1, 1), 1.0, 1.0, 13.0, np.array([1.0]))   # M = 1
+        print("case lost basis", form, k, b, flush=True)
+        if form == "count":
+            go = lambda: ec.count(Ad, W.PrecSpec("none"), -2.0, 1.5, Vd, k)
+        elif form == "smooth":
+            go = lambda: ec.count(Ad, M1, -2.0, 1.5, Vd, k, smooth_w=0.1)
+        elif form == "grad":
+            go = lambda: ec.smooth_forward(Ad, M1, -2.0, 1.5, Vd, k, 0.1)[0]
+        else:
+            go = lambda: ec.count_batched(Ad, W.PrecSpec("none"), [N], np.array([[-2.0, 1.5]]), Vd, k)
+        if b == 1e-9:
+            with pytest.raises(ec.EcntError) as e:
+                go()
+            assert e.value.status == ec.ECNT_EDEVICE and "orthogonality" in str(e.value)
+        else:
+            r = go()
+            est = float(np.ravel(r.counts)[0]) if form == "batch" else r.estimate
+            assert abs(est - 1.0) <= 1e-8
+
+
+def test_weak_couplings_in_fp32_storage(ec):
+    """FP32 storage: couplings that small are below its breakdown bound, so the
+    column stops there, with what it has; couplings above it keep the basis."""
+    for b, ku in ((1e-5, 1), (1e-2, 40)):
+        A, v, a = weak_chain(160, b)
+        r = gpu_count(ec, A, W.PrecSpec("none"), -2.0, 1.5, v, 40, vec="f32")
+        print("case fp32", b, r.k_used.tolist(), flush=True)
+        assert r.k_used.tolist() == [ku] * 2
+        assert np.max(np.abs(r.per_probe.cpu().numpy() - [0.0, 1.0])) <= 1e-4
