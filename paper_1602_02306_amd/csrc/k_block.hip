@@ -764,6 +764,7 @@ __global__ __launch_bounds__(NMAX) void k_blk_dc(int nblk, int c_off, int k, dou
         }
         s_out[col0 + t] = sum;
         minabs[col0 + t] = lo;
+        if (t == 0 && w.stray) atomicOr(&flags[1], 1);
     }
 }
 

@@ -319,6 +319,7 @@ __global__ __launch_bounds__(NMAX * P) void k_tridiag_dc(int NC, int C, int ld, 
         }
         s_all[gidx] = nu[vc] * s;
         minabs_all[gidx] = mn;
+        if (w.stray) atomicOr(&flags[1], 1);
     }
 }
 

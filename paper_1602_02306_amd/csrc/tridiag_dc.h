@@ -32,6 +32,7 @@ struct DcLds {
     double sd[NMAX], sz[NMAX], sf[NMAX], sl[NMAX];   // a merge's entries in ascending order
     double mu[NMAX], zh[NMAX];
     int perm[NMAX], src[NMAX], act[NMAX], org[NMAX], close[NMAX];
+    int stray;   // a root's iteration ended at its limit
 };
 
 // 1/x for a finite normal x: the hardware estimate y0 and the series 1/(1 - e) =
@@ -71,15 +72,18 @@ __device__ __forceinline__ int team_count(int x)
 
 // Root j of 1 + rho sum_i z_i^2 / (d_i - x) for ascending poles d_0..d_{K-1}: the
 // pole it is measured from and the offset.  Lane p of the P that share the root
-// takes the poles p, p + P, ...
+// takes the poles p, p + P, ...  False where the iteration ends at its limit (most
+// roots take 2 to 8 steps; bracketed halving down to what deflation leaves takes
+// about 50, 48 being the most over 12 million roots of glued, graded, clustered
+// and random matrices).
 template <int P>
-__device__ __forceinline__ void dc_secular(const double *d, const double *z, int K, int j, int p0, double rho,
+__device__ __forceinline__ bool dc_secular(const double *d, const double *z, int K, int j, int p0, double rho,
                                            int &org, double &mu)
 {
     org = j;
     if (K == 1) {
         mu = rho * z[0] * z[0];
-        return;
+        return true;
     }
     const bool last = j == K - 1;
     double lo, hi;
@@ -121,7 +125,7 @@ __device__ __forceinline__ void dc_secular(const double *d, const double *z, int
         phi = rho * team_sum<P>(phi);
         dphi = rho * team_sum<P>(dphi);
         const double f = 1.0 + psi + phi;
-        if (fabs(f) <= 8.0 * DBL_EPSILON * (1.0 + fabs(psi) + fabs(phi))) break;
+        if (fabs(f) <= 8.0 * DBL_EPSILON * (1.0 + fabs(psi) + fabs(phi))) return true;
         if (f < 0.0) lo = mu;
         else hi = mu;
         const double p = (d[j] - d0) - mu;
@@ -136,9 +140,10 @@ __device__ __forceinline__ void dc_secular(const double *d, const double *z, int
         }
         double x = mu + eta;
         if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);   // also where eta is not a number
-        if (x == mu) break;
+        if (x == mu) return true;
         mu = x;
     }
+    return false;
 }
 
 struct DcNoRows {
@@ -151,7 +156,7 @@ struct DcNoRows {
 };
 
 // On return s.D[0..N-1] are the eigenvalues (in no order), s.F the entries of
-// the first row of the eigenvector matrix.  a, b: LDS, with entries of
+// the first row of the eigenvector matrix, s.stray whether to report a failure.  a, b: LDS, with entries of
 // magnitude at most 1, b >= 0.  NMAX >= N; the workgroup has P NMAX threads, P
 // neighbouring ones per entry (their sums over the poles are short chains of
 // dependent instructions, so more lanes mean less time as long as the chip has
@@ -162,6 +167,7 @@ __device__ __forceinline__ void tridiag_dc(int N, const double *a, const double 
 {
     constexpr double tol = 4.0 * DBL_EPSILON;
     const int t = threadIdx.x / P, p0 = threadIdx.x % P;
+    if (threadIdx.x == 0) s.stray = 0;
     __syncthreads();
     if (t < N && p0 == 0) {
         double d = a[t];
@@ -261,8 +267,9 @@ __device__ __forceinline__ void tridiag_dc(int N, const double *a, const double 
         double mu = 0.0;
         int org = 0;
         if (root) {
-            dc_secular<P>(s.D + lo, s.Z + lo, K, t - lo, p0, rho, org, mu);
+            const bool met = dc_secular<P>(s.D + lo, s.Z + lo, K, t - lo, p0, rho, org, mu);
             if (p0 == 0) {
+                if (!met) s.stray = 1;
                 s.mu[t] = mu;
                 s.org[t] = lo + org;
             }
