@@ -1067,3 +1067,55 @@ def test_weak_couplings_in_fp32_storage(ec):
         print("case fp32", b, r.k_used.tolist(), flush=True)
         assert r.k_used.tolist() == [ku] * 2
         assert np.max(np.abs(r.per_probe.cpu().numpy() - [0.0, 1.0])) <= 1e-4
+
+
+def _spread_matrix(kind, N):
+    """Tridiagonal matrices on whose eigenvectors e_1 is spread out, and the
+    smallest coupling."""
+    b = np.ones(N - 1)
+    if kind == "chain":         # a band of single eigenvalues
+        return 0.1 * np.random.default_rng(N).standard_normal(N), b, 1.0
+    if kind == "glued":         # copies of one block: clusters of width 1e-6
+        b[20::21] = 1e-6
+        return np.zeros(N), b, 1e-6
+    w = float(kind)             # pairs, weakly coupled: two clusters, e_1 in all of both
+    b[1::2] = w
+    return np.zeros(N), b, w
+
+
+@pytest.mark.parametrize("kind", ["chain", "1e-3", "1e-6", "glued"])
+@pytest.mark.parametrize("N", [17, 32, 33, 64, 65, 128, 129, 256, 257, 512])
+def test_quadrature_weights_inside_clusters(ec, kind, N):
+    """The eigensolve's cumulative weights at shifts that split the mass of e_1
+    (reference between 0.02 and 0.98, the widest such gaps), clusters and
+    deflation included.  Lanczos is backward stable, T = Q^T (A + E) Q with |E| of
+    a few N eps |A|, and so is the eigensolve: a weight moves by N eps |A| / gap
+    times a small constant.  T itself moves by the turn of its vectors, up to
+    N^2 eps / the smallest coupling: the coefficients are those of the matrix."""
+    a, b, w = _spread_matrix(kind, N)
+    T = np.diag(a) + np.diag(b, 1) + np.diag(b, -1)
+    lam, Z = np.linalg.eigh(T)
+    cum = np.cumsum(Z[0] ** 2)[:-1]
+    gaps = np.where((cum > 0.02) & (cum < 0.98), np.diff(lam), 0.0)
+    at = np.sort([i for i in np.argsort(gaps)[-8:] if gaps[i] > 0.0])
+    assert len(at) >= 3
+    taus = 0.5 * (lam[at] + lam[at + 1])
+    rp, ci = [0], []
+    for r in range(N):
+        ci += [c for c in (r - 1, r, r + 1) if 0 <= c < N]
+        rp.append(len(ci))
+    val = np.array([T[r, c] for r in range(N) for c in ci[rp[r]:rp[r + 1]]])
+    A = W.CSR(N, np.array(rp, np.int32), np.array(ci, np.int32), val)
+    V = torch.zeros(N, 1, dtype=torch.float64, device="cuda")
+    V[0, 0] = 1.0
+    print("case weights", kind, N, flush=True)
+    r = ec.negcounts(ec.upload_csr(A), W.PrecSpec("none"), taus, V, N)
+    tol = 64 * N * 2.3e-16 * 4.0 / gaps[at]
+    s = r.per_probe.cpu().numpy().ravel()
+    assert np.all(np.abs(s - cum[at]) <= tol), (s, cum[at], tol)
+    r = ec.count(ec.upload_csr(A), W.PrecSpec("none"), float(taus[0]), float(taus[-1]), V, N)
+    ku = int(r.k_used[0])
+    assert ku == N or kind == "glued"
+    coef = N * N * 2.3e-16 / w
+    assert np.max(np.abs(r.alpha.cpu().numpy()[:ku, 0] + taus[0] - a[:ku])) <= coef
+    assert np.max(np.abs(r.beta.cpu().numpy()[1:ku, 0] - b[:ku - 1])) <= coef
