@@ -501,7 +501,7 @@ static void plan_onesweep(Plan &p, SegHost &sh)
     p.onesweep = 1;
     p.part_rows = p.k + 2;
     while (plan_layout(p, nullptr) > most) {
-        if (p.rpc >= p.n) {   // as short as it gets
+        if (p.rpc >= p.max_rows) {   // one chunk per segment: as few as there can be
             p.onesweep = 0;
             p.part_rows = kPartRows;
             p.rpc = rpc;

@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 import subprocess
+import time
 
 import numpy as np
 import pytest
@@ -224,3 +225,26 @@ def test_hbm_probe_rejects_bad_arguments_on_host():
                                     (0, 0x1000, 1 << 20, 1), (1, 0x1000, 1 << 30, 0)]:
         rc = lib.ecnt_hbm_probe(kind, buf, nbytes, reps, None, ctypes.byref(g))
         assert rc == ec.ECNT_EINVAL, ec.last_error()
+
+
+def test_batch_sizing_of_many_problems_is_one_pass():
+    """Sizing a batch is linear in its problems whatever k: the search for longer
+    row chunks ends where every problem is one chunk (before, it went on to the
+    batch's whole length, 100 passes over the problems)."""
+    lib = ec.load()
+    nprob, n = 50000, 112
+    taus = np.zeros(2)
+    items = (ec.BatchItemT * nprob)()
+    for b in range(nprob):
+        items[b] = ec.BatchItemT(n, (ctypes.c_int32 * 3)(1, 1, n), 0, taus.ctypes.data)
+    ps, _ = ec.prec_struct(W.PrecSpec("none"))
+
+    def best(k):
+        o = ec.opts_struct(k)
+        ts = []
+        for _ in range(10):
+            t = time.perf_counter()
+            assert lib.ecnt_batch_workspace_bytes(items, nprob, 2, 1, ctypes.byref(ps), ctypes.byref(o)) > 0
+            ts.append(time.perf_counter() - t)
+        return min(ts)
+    assert best(100) <= 4.0 * best(1)
