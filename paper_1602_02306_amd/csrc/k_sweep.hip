@@ -34,12 +34,19 @@
 
 namespace ecnt {
 
-// Rows of the partial sums of a chunk: 0 u.u, 1 + l slot_l.u (l < i), i + 1 u.z
+// Rows of the partial sums of a chunk: 0 u.u, 1 + l slot_l.u (l < i), i + 1 u.z;
+// step 0: 0 v.v, 1 v.z, 2 z.z
 
-// scale[vc]: a power of two near 1 / |u| for the sums u.z.  u and z = C u
-// are of the order of |C| and |C|^2 from step 1 on, so u.z would leave the range of
-// a double at |C| = 2^340 already, where |u|^2 does at 2^511.  Taken from the chunk
-// sums of |u|^2 (row 0) before the first two sums, the second for all later steps.
+// A power of two near 1 / sqrt(x) (1 where there is none).  u and z = C u are of
+// the order of |C| and |C|^2 from step 1 on, so u.z would leave the range of a
+// double at |C| = 2^340 already, where |u|^2 does at 2^511: its terms are taken
+// times near 1 / |C|, in step 0 near 1 / |v|.
+__device__ __forceinline__ double uz_scale(double x)
+{
+    return x > 0.0 && x <= DBL_MAX ? ldexp(1.0, -(ilogb(x) / 2)) : 1.0;
+}
+
+// scale[vc] for step 0, from the chunk sums of |v|^2 (row 0)
 __global__ __launch_bounds__(64 * kFinWaves) void k_uz_scale(int C, int nseg, int rows,
                                                              const int64_t *__restrict__ seg_chunk,
                                                              const double *__restrict__ part,
@@ -49,11 +56,12 @@ __global__ __launch_bounds__(64 * kFinWaves) void k_uz_scale(int C, int nseg, in
     const bool valid = vc < nseg * C;
     const int seg = valid ? vc / C : 0, c = valid ? vc - seg * C : 0;
     const double uu = block_chunk_sum(part, rows, C, 0, c, seg_chunk[seg], seg_chunk[seg + 1], valid);
-    if (!valid || threadIdx.x >= 64) return;
-    scale[vc] = uu > 0.0 && uu <= DBL_MAX ? ldexp(1.0, -(ilogb(uu) / 2)) : 1.0;
+    if (valid && threadIdx.x < 64) scale[vc] = uz_scale(uu);
 }
 
-// part[chunk][row][c] = scale * sum over the chunk's rows of U * Z
+// part[chunk][row][c] = scale * sum over the chunk's rows of U * Z; FIRST (step 0):
+// and in the next row scale^2 * sum of Z * Z
+template <bool FIRST>
 __global__ __launch_bounds__(256) void k_dot_uz(int C, int nct, int64_t rpc, int nseg,
                                                 const int64_t *__restrict__ seg_row,
                                                 const int64_t *__restrict__ seg_chunk,
@@ -62,7 +70,7 @@ __global__ __launch_bounds__(256) void k_dot_uz(int C, int nct, int64_t rpc, int
                                                 const double *__restrict__ scale, int rows, int row,
                                                 double *__restrict__ part)
 {
-    __shared__ double red[4][64];
+    __shared__ double red[4][64], red2[FIRST ? 4 : 1][64];
     const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
     const int ct = (int)(L % nct);
     const int64_t chunk = L / nct;
@@ -71,18 +79,23 @@ __global__ __launch_bounds__(256) void k_dot_uz(int C, int nct, int64_t rpc, int
     const int seg = find_seg(seg_chunk, nseg, chunk);
     const int64_t r0 = seg_row[seg] + (chunk - seg_chunk[seg]) * rpc;
     const int64_t r1 = min(seg_row[seg + 1], r0 + rpc);
-    double a = 0.0;
+    double a = 0.0, b = 0.0;
     if (c < C) {
         const double sc = scale[(size_t)seg * C + c];
         for (int64_t r = r0 + wv; r < r1; r += 4) {
             const size_t e = (size_t)r * C + c;
-            a += (U[e] * sc) * Z[e];
+            const double z = Z[e];
+            a += (U[e] * sc) * z;
+            if (FIRST) b += (z * sc) * (z * sc);
         }
     }
     red[wv][lane] = a;
+    if (FIRST) red2[FIRST ? wv : 0][lane] = b;
     __syncthreads();
-    if (wv == 0 && c < C)
-        part[((size_t)chunk * rows + row) * C + c] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (wv != 0 || c >= C) return;
+    double *P = part + ((size_t)chunk * rows + row) * C + c;
+    P[0] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if constexpr (FIRST) P[C] = (red2[0][lane] + red2[1][lane]) + (red2[2][lane] + red2[3][lane]);
 }
 
 // Chunk sums of rows 0..gridDim.y-1, each left in the segment's first chunk.
@@ -105,7 +118,7 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
                                                    double eps_vec,
                                                    const int64_t *__restrict__ seg_chunk,
                                                    const double *__restrict__ part,
-                                                   const double *__restrict__ scale,
+                                                   double *__restrict__ scale,
                                                    double *__restrict__ nu, double *__restrict__ sig,
                                                    double *__restrict__ alpha,
                                                    double *__restrict__ beta,
@@ -179,6 +192,7 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
         nu[v] = uu;
         beta[v] = 0.0;
         kused[(size_t)seg * ku_ld + ku_off + c] = on ? k : 0;
+        scale[v] = uz_scale(S[(size_t)2 * C]);   // |C v|^2 / |v|^2 to a factor of 4
     } else {
         alpha[(size_t)(i - 1) * NC + v] = was ? a_last : 0.0;
         beta[(size_t)i * NC + v] = was ? b : 0.0;
@@ -431,12 +445,17 @@ __global__ __launch_bounds__(64 * WMAX) void k_sweep(int C, int nct, int64_t rpc
 
 void launch_dot_uz(const Plan &p, int i, const void *z, hipStream_t st)
 {
-    if (i < 2)
+    const unsigned grid = (unsigned)((int64_t)p.nchunk * p.nct);
+    const double *u = (const double *)p.basis + (size_t)i * slot_elems(p);
+    if (i == 0) {
         k_uz_scale<<<(p.nseg * p.C + 63) / 64, 64 * kFinWaves, 0, st>>>(p.C, p.nseg, p.part_rows, p.seg_chunk,
                                                                         p.part, p.kappa);
-    k_dot_uz<<<(unsigned)((int64_t)p.nchunk * p.nct), 256, 0, st>>>(
-        p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, (const double *)p.basis + (size_t)i * slot_elems(p),
-        (const double *)z, p.kappa, p.part_rows, i + 1, p.part);
+        k_dot_uz<true><<<grid, 256, 0, st>>>(p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, u,
+                                             (const double *)z, p.kappa, p.part_rows, 1, p.part);
+    } else {
+        k_dot_uz<false><<<grid, 256, 0, st>>>(p.C, p.nct, p.rpc, p.nseg, p.seg_row, p.seg_chunk, u,
+                                              (const double *)z, p.kappa, p.part_rows, i + 1, p.part);
+    }
 }
 
 // Chunk sums of the first `rows` rows.
@@ -448,7 +467,7 @@ static void sweep_sum(const Plan &p, int rows, hipStream_t st)
 
 void launch_sweep_fin(const Plan &p, int i, hipStream_t st)
 {
-    sweep_sum(p, i < p.k ? i + 2 : i + 1, st);
+    sweep_sum(p, i == 0 ? 3 : (i < p.k ? i + 2 : i + 1), st);
     const size_t lds = sizeof(double) * 64 * ((size_t)i + 16);
     if (lds > (size_t)64 << 10)   // more than the default of dynamic LDS (not a stream operation)
         (void)hipFuncSetAttribute((const void *)k_sweep_fin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
