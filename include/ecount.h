@@ -116,7 +116,8 @@ typedef enum {
  * Each call first writes L and L^T into its workspace as bands of 256 values
  * per row (2 * 256 * 8 bytes per row and shift).  With FP64 vectors and few
  * columns the rows are solved in parts, which takes 1 MiB more per inner part
- * and shift; a workspace that holds the bands only solves them whole. */
+ * and shift and 4 KiB per part and column; a workspace that holds the bands only
+ * solves them whole. */
 typedef struct {
     const int32_t *perm;
     const int32_t *l_row_ptr;

@@ -22,7 +22,10 @@
 // though, where plain substitution has only a residual of rounding; so there
 // is one step of refinement: the sums that part p really leaves behind minus
 // s_{p+1}, d_{p+1}, go through the same chain (e_{p+1} = d_{p+1} - K_p e_p) and
-// every part adds its solution with right-hand side 0 and e_p coming in.
+// every part adds its solution with right-hand side 0 and e_p coming in.  Y is
+// stored and then added to, so the residual is a few roundings more than plain
+// substitution's: componentwise 1.1e-16 to 9e-16 against 0.6e-16 to 2.8e-16 over
+// factors with |K_p| up to 240, dropping none to 0.5 (1e-13 without the step).
 // (Solving again from s_p + e_p does not do: a pass repeats its own rounding
 // only for the same input, and that again is a forward error.)
 #include <type_traits>
@@ -182,8 +185,8 @@ struct LdlSolveSet {
 // staged band rows (8 steps at a time in two buffers, one barrier per 8 steps;
 // each wavefront loads and stages two of them), so the band is read once per
 // four columns.  Three buffers, which let a step read the next batch's first
-// coefficients ahead, measured the same.  A pass over 832 rows of 50 columns
-// takes 73 us, about 80 ns a row; a single wavefront alone needs 71 ns.
+// coefficients ahead, measured the same.  A pass over 17 parts of 960 rows, 50
+// columns, takes 61 to 67 us, about 66 ns a row.
 //
 // MODE 0: a whole solve in one part.
 // MODE 1: the part with nothing carried in, for its carry out: part p's goes
@@ -385,13 +388,13 @@ __global__ __launch_bounds__(256) void k_ldl_solve(int64_t n, int C, int64_t R, 
 }
 
 // The chain of the carried sums, one workgroup per column, p = 1..P-2:
-// v[p + 1] -= K_p v[p], from v[1] as it is, or from 0 with REFINE (s_1 is exact).  K_p is stored by columns (K[p - 1][j][i]); thread
-// (i, part) takes half of the j.  Bound: K_p's 512 KiB through one CU's
-// L2 port, so the loads run ahead of the products by one batch and do not wait
-// for the sums.
+// v[p + 1] -= K_p v[p], from v[1] as it is, or from 0 with REFINE (s_1 is exact).
+// K_p is stored by columns (K[p - 1][j][i]); a thread takes a quarter of the j for
+// two i.  Bound: K_p's 512 KiB through one CU's L2 port, so the loads run ahead of
+// the products by one batch and do not wait for the sums.
 struct LdlChainSet {
     int nsh;
-    int lo[kMaxShifts], hi[kMaxShifts];
+    int hi[kMaxShifts];
     const double *K[kMaxShifts];
 };
 
@@ -463,17 +466,18 @@ int64_t ldl_part_rows(int64_t n, int P) { return ((n + P - 1) / P + 63) / 64 * 6
 // Parts of the rows: the count with the least estimated time of a solve, in
 // cycles (64-bit vectors only: the 32-bit form rounds each y once).  A step of
 // the walk takes about 190 cycles, or 60 of issue per wavefront on a SIMD; a
-// chain step 12500 (512 KiB through one CU's port: 5.2 us); K_p costs 256 more
+// chain step 12500 (512 KiB through one CU's port: 5.0 us); K_p costs 256 more
 // columns per part and triangle once per call, spread over 2 k solves.  n =
-// 16129, 50 columns: 20 parts, 422 us a solve, against 1140 us whole; below
-// about 4000 rows, or with a thousand columns, it stays whole.
+// 16129, 50 columns, k = 6: 17 parts of 960 rows, 343 us a solve (three passes of
+// 64 us, two chains of 75), against 1140 us whole; below about 2500 rows, or with
+// a thousand columns, it stays whole.
 void ldl_plan_parts(Plan &p)
 {
     p.ldl_parts = 1;
     if (p.prec_kind != 3 || p.vec_f32) return;
     const double cols = p.wave_cols, whole = p.n * ldl_row_cycles(cols);
     double best = 0.8 * whole;
-    for (int P = 2; P <= 64; ++P) {
+    for (int P = 4; P <= 64; ++P) {   // (three walks of n / P rows: fewer parts gain nothing)
         const int64_t R = ldl_part_rows(p.n, P);
         if (R < kRing || (P - 1) * R >= p.n) continue;
         const double setup = R * ldl_row_cycles((double)kRing * (P - 2)) * p.S / p.k;
@@ -488,7 +492,7 @@ void ldl_plan_parts(Plan &p)
 
 size_t ldl_chain_doubles(const Plan &p)   // K of both triangles of every shift
 {
-    return p.ldl_parts > 2 ? (size_t)2 * p.S * (p.ldl_parts - 2) * kRing * kRing : 0;
+    return p.ldl_parts > 1 ? (size_t)2 * p.S * (p.ldl_parts - 2) * kRing * kRing : 0;
 }
 
 size_t ldl_carry_doubles(const Plan &p)
@@ -523,7 +527,7 @@ void launch_ldl_eblocks(const Plan &p, hipStream_t st)
         k_ldl_band_fill<<<(unsigned)((p.n + 3) / 4), 256, 0, st>>>(
             p.n, p.ldl[s].nnz, p.ldl[s].lrp, p.ldl[s].lci, p.ldl[s].lval, bf, bb);
     }
-    if (p.ldl_parts <= 2) return;
+    if (p.ldl_parts == 1) return;
     // K_p, p = 1..P-2, of both triangles: a shift at a time (each fills the chip)
     for (int s = 0; s < p.S; ++s) {
         LdlSolveSet set;
@@ -568,9 +572,8 @@ static void ldl_t(const Plan &p, int what, const void *X, const double *xs, void
             set.lo[k] = lo;
             set.hi[k] = hi;
             set.band[k] = what == 1 ? bb : bf;
-            ch.lo[k] = lo;
             ch.hi[k] = hi;
-            ch.K[k] = p.ldl_parts > 2 ? chain_of(p, s, what == 1 ? 0 : 1) : nullptr;
+            ch.K[k] = p.ldl_parts > 1 ? chain_of(p, s, what == 1 ? 0 : 1) : nullptr;
         }
         ch.nsh = set.nsh;
         if (set.nsh == 0) return;
@@ -597,9 +600,8 @@ static void ldl_t(const Plan &p, int what, const void *X, const double *xs, void
             return;
         }
         solve(std::integral_constant<int, 1>{}, 0, P - 1);
-        if (P > 2) k_ldl_chain<false><<<p.C, 512, 0, st>>>(p.C, P, ch, p.ldl_carry);
+        k_ldl_chain<false><<<p.C, 512, 0, st>>>(p.C, P, ch, p.ldl_carry);
         solve(std::integral_constant<int, 3>{}, 1, P - 1);
-        if (P == 2) return;   // part 1 started from what part 0 left behind
         k_ldl_chain<true><<<p.C, 512, 0, st>>>(p.C, P, ch, diff);
         solve(std::integral_constant<int, 4>{}, 2, P - 2);
         return;
