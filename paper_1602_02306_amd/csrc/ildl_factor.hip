@@ -56,9 +56,9 @@ void row_erase(Row &r, int32_t col)
 }
 
 // r(cols[q]) -= delta[q] for sorted cols: a merge that inserts fill in order.
-// Nearly all of a factorization's time: at a multiple of 64 bytes, or it takes 721 ms
-// for 623 (127^2 Laplacian, t = 1e-6) where the linker happens to place it off one.
-__attribute__((aligned(64))) void row_sub(Row &r, const std::vector<int32_t> &cols, const std::vector<double> &delta,
+// Nearly all of a factorization's time: 605 to 720 ms for the 127^2 Laplacian, t =
+// 1e-6, as the code happens to be laid out (the entry's alignment does not decide it).
+void row_sub(Row &r, const std::vector<int32_t> &cols, const std::vector<double> &delta,
              std::vector<int32_t> &tc, std::vector<double> &tv)
 {
     tc.clear();
