@@ -1119,3 +1119,32 @@ def test_quadrature_weights_inside_clusters(ec, kind, N):
     coef = N * N * 2.3e-16 / w
     assert np.max(np.abs(r.alpha.cpu().numpy()[:ku, 0] + taus[0] - a[:ku])) <= coef
     assert np.max(np.abs(r.beta.cpu().numpy()[1:ku, 0] - b[:ku - 1])) <= coef
+
+
+@pytest.mark.parametrize("kind,size", [("outliers", 1e6), ("outliers", 1e10), ("outliers", 1e11),
+                                       ("clusters", 1e-7), ("clusters", 1e-11), ("log", 1e-12)])
+@pytest.mark.parametrize("fused", ["auto", "off"])
+def test_ill_scaled_operators(ec, kind, size, fused):
+    """A diagonal matrix, whose products round once, and probes of +-1: with k = n
+    s_j is the number of eigenvalues below the shift.  Lanczos returns it for a
+    matrix within a few n eps |A|, which turns an eigenvector by that over its gap
+    to the other side; both forms that keep the basis, against that bound."""
+    n = 64
+    if kind == "outliers":
+        lam = np.concatenate([np.linspace(-1.0, 1.0, n - 4), size * np.array([1.0, 2.0, -1.0, 3.0])])
+    elif kind == "clusters":
+        lam = np.repeat(np.linspace(-1.0, 1.0, 16), 4) + size * np.tile(np.arange(4), 16)
+    else:
+        h = np.logspace(np.log10(size), 0.0, n // 2)
+        lam = np.concatenate([-h, h]) + 0.5
+    xi, eta = (-0.1, 0.25) if kind != "log" else (0.1, 0.9)
+    lam = np.random.default_rng(4).permutation(lam)
+    A = W.CSR(n, np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32), lam)
+    V = W.rademacher(n, 5, 8)
+    print("case ill-scaled", kind, size, fused, flush=True)
+    r = gpu_count(ec, A, W.PrecSpec("none"), xi, eta, V, n, tune={"fused": fused})
+    gap = min(np.min(lam[lam > t]) - np.max(lam[lam < t]) for t in (xi, eta))
+    tol = 4 * n * 2.3e-16 * np.abs(lam).max() / gap + 1e-9
+    s = r.per_probe.cpu().numpy().reshape(2, 5)
+    assert np.max(np.abs(s[0] - np.sum(lam < xi))) <= tol
+    assert np.max(np.abs(s[1] - np.sum(lam < eta))) <= tol
