@@ -1175,7 +1175,9 @@ static void stencil_flags(const Plan &p, const void *X, const double *xs, double
                           bool in_is_x, double cbd, double cbo, const void *Z, double cz, void *out,
                           hipStream_t st)
 {
-    if (!IN) {
+    if (!IN && Z) {   // the accumulation of a polynomial in Clenshaw's form
+        stencil_t<T, VW, TX, TY, false, true, true>(p, X, xs, cx, IN, false, 0, 0, Z, cz, out, st);
+    } else if (!IN) {
         stencil_t<T, VW, TX, TY, false, true, false>(p, X, xs, cx, IN, false, 0, 0, nullptr, 0, out, st);
     } else if (IN == X && !Z) {
         stencil_t<T, VW, TX, TY, true, false, false>(p, X, xs, cx, IN, in_is_x, cbd, cbo, nullptr, 0, out, st);

@@ -1148,3 +1148,16 @@ def test_ill_scaled_operators(ec, kind, size, fused):
     s = r.per_probe.cpu().numpy().reshape(2, 5)
     assert np.max(np.abs(s[0] - np.sum(lam < xi))) <= tol
     assert np.max(np.abs(s[1] - np.sum(lam < eta))) <= tol
+
+
+@pytest.mark.parametrize("coef", [[0.4], [0.5, -0.1], [0.5, -0.1, 0.0], [0.5, -0.12, 0.04, -0.02, 0.0]])
+@pytest.mark.parametrize("k", [2, 17])
+def test_smooth_gradient_of_polynomials_without_product_form(ec, coef, k):
+    """Degrees 0 and 1 and a vanishing leading coefficient are applied by
+    Clenshaw's recurrence; the reverse sweep adds M u to what is there."""
+    dims = (5, 6, 7)
+    wl = W.Workload("g", dims, "wells", 2, -8.0, -2.0, "cheb", 9, k, smooth_w=0.5)
+    P = W.make_problem(wl)
+    P.prec = W.PrecSpec("cheb", dims, 1.0, 1.0, 13.0, np.array(coef))
+    print("case grad clenshaw", coef, k, flush=True)
+    _grad_vs_oracle(ec, P, -3.0, 1.0, W.make_probes(wl), k, 0.5, 31)
