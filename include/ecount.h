@@ -53,11 +53,7 @@ typedef int32_t ecnt_status;
 #define ECNT_EINVAL (-1)       /* invalid argument (null pointer, bad size, xi >= eta, ...) */
 #define ECNT_ENOTHPD (-2)      /* preconditioner not HPD (Jacobi pivot a_rr == tau)       */
 #define ECNT_EWORKSPACE (-3)   /* workspace missing or smaller than ecnt_workspace_bytes() */
-#define ECNT_EDEVICE (-4)      /* HIP runtime error, the tridiagonal solver diverged, or
-                                  the Lanczos basis lost its orthogonality: FP64 with
-                                  k > 128, gradients and the smoothed counts they serve,
-                                  on operators whose beta stays below about 1e-7 of the
-                                  norm (the other FP64 forms keep the basis) */
+#define ECNT_EDEVICE (-4)      /* HIP runtime error, or the tridiagonal solver diverged   */
 #define ECNT_EUNSUPPORTED (-5) /* valid request outside what the library supports        */
 
 typedef enum { ECNT_F64 = 0, ECNT_F32 = 1 } ecnt_dtype;
@@ -211,9 +207,14 @@ typedef struct {
                              rounding of 0 makes h(theta) tie-sensitive */
     double *per_probe;    /* device, nshift*m: s_j(tau) = |v_j|^2 sum_{theta<0} z(1)^2,
                              shift-major (all probes of shift 0 first)             */
-    int32_t *k_used;      /* device, nshift*m: steps actually taken (< k after an
-                             invariant Krylov space was found)                     */
-    double *alpha;        /* device, k x (nshift*m): alpha_1..alpha_k per column    */
+    int32_t *k_used;      /* device, nshift*m: steps used (< k after an invariant
+                             Krylov space was found, or before a vector that lost
+                             its orthogonality: FP64 with k > 128, gradients, the
+                             smoothed counts they serve, batches of many small
+                             problems with k > 30, where beta stays below about
+                             1e-7 of the norm; other FP64 forms keep the basis)     */
+    double *alpha;        /* device, k x (nshift*m): alpha_1..alpha_k per column, zeros
+                             past k_used                                            */
     double *beta;         /* device, (k+1) x (nshift*m): beta_1 = 0, beta_2..beta_{k+1} */
 } ecnt_info;
 

@@ -182,10 +182,11 @@ __global__ __launch_bounds__(64) void k_dots(int C, int nct, int64_t rpc, int ns
 // holds q_i sums alpha_i itself; the others read it, that launch running first.
 // One pass a step does not hold the basis under couplings that stay below
 // sqrt(eps) of the norm: each step multiplies what is left of the error by
-// |alpha| / beta.  p_l of an active column past kLostBasis is reported (flags[1],
-// 2): from there on it is of order one within a step or two.  (s_j is off by about
-// 0.2 |v_j|^2 p; p stays below 1e-11 for beta >= 1e-5 of the norm, and below 4e-4
-// with four eigenvalues 1e10 times the others.)
+// |alpha| / beta.  Where p_l of an active column passes kLostBasis, q_i is lost: it
+// is of order one within a step or two, s_j off by about 0.2 |v_j|^2 p, and the
+// column's result is that of the steps before (kused).  (p stays below 1e-11 for
+// beta >= 1e-5 of the norm, and below 4e-4 with four eigenvalues 1e10 times the
+// others.)
 // Arrays indexed [row][nseg*C].
 constexpr double kLostBasis = 0.1;
 
@@ -194,7 +195,7 @@ __global__ void k_dots_fin(int C, int nseg, int step, int l0, int nb, int k,
                            const double *__restrict__ sig, const int32_t *__restrict__ active,
                            double *__restrict__ cf, double *__restrict__ alpha,
                            double *__restrict__ gall, double *__restrict__ pall, int gram,
-                           int32_t *__restrict__ flags)
+                           int32_t *__restrict__ kused, int ku_ld, int ku_off)
 {
     // block (x: 64 virtual columns, y: basis vector l), kFinWaves wavefronts over the chunks
     const int NC = nseg * C;
@@ -219,7 +220,8 @@ __global__ void k_dots_fin(int C, int nseg, int step, int l0, int nb, int k,
         const double a = arow < nb ? (active[vc] ? sa * si : 0.0) : alpha[(size_t)(step - 1) * NC + vc];
         pe = sp * sg * si - (l0 + l == step - 1 ? 1.0 : 0.0);
         c_l = g - a * pe;
-        if (active[vc] && fabs(pe) > kLostBasis) atomicOr(&flags[1], 2);
+        if (active[vc] && fabs(pe) > kLostBasis)
+            atomicMin(&kused[(size_t)seg * ku_ld + ku_off + c], step - 1);
     }
     cf[(size_t)(l0 + l) * NC + vc] = c_l * sg;
     if (l0 + l == step - 1) alpha[(size_t)(step - 1) * NC + vc] = active[vc] ? g : 0.0;
@@ -326,7 +328,8 @@ __global__ void k_norm_fin(int C, int nseg, int step, double eps_vec,
         beta[(size_t)i * C_ + c] = b;
         if (b <= 1e3 * eps_vec * rm) {
             active[c] = 0;
-            kused[(size_t)seg * ku_ld + ku_off + cc] = i;
+            int32_t &ku = kused[(size_t)seg * ku_ld + ku_off + cc];
+            ku = min(ku, i);
             sig[(size_t)i * C_ + c] = 0.0;
             kappa[c] = 0.0;
         } else {
@@ -444,7 +447,7 @@ void launch_dots_fin(const Plan &p, int step, int l0, int nb, bool gram, hipStre
     const int NC = p.nseg * p.C;
     k_dots_fin<<<dim3((NC + 63) / 64, nb), 64 * kFinWaves, 0, st>>>(
         p.C, p.nseg, step, l0, nb, p.k, p.seg_chunk, p.part, p.sig, p.active, p.cf, p.alpha,
-        p.g_gall, p.g_pall, gram ? 1 : 0, p.flags);
+        p.g_gall, p.g_pall, gram ? 1 : 0, p.kused, p.Ct, p.c_off);
 }
 
 void launch_update(const Plan &p, int step, int l0, int nb, bool first, bool last, hipStream_t st)

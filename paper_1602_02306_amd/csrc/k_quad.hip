@@ -81,6 +81,8 @@ __global__ __launch_bounds__(64) void k_tridiag(int NC, int C, int ld, int off, 
     int hi = N - 1;
     int iter = 0;
     bool failed = false;
+    for (int i = ku; i < k; ++i)   // the steps after a lost vector: an error if they left the range
+        failed = failed || !(fabs(alpha[(size_t)i * C + c]) <= DBL_MAX) || !(fabs(beta[(size_t)i * C + c]) <= DBL_MAX);
     while (hi > 0) {
         if (fabs(B_(hi - 1)) <= DBL_EPSILON * (fabs(A_(hi - 1)) + fabs(A_(hi))) ||
             fabs(B_(hi - 1)) < DBL_MIN) {
@@ -276,7 +278,9 @@ __global__ __launch_bounds__(NMAX * P) void k_tridiag_dc(int NC, int C, int ld, 
     }
     // scaled to entries of magnitude at most 1
     const double m0 = fmax(fabs(a), fabs(b));
-    const bool bad = !(fabs(a) <= DBL_MAX) || !(fabs(b) <= DBL_MAX);
+    bool bad = !(fabs(a) <= DBL_MAX) || !(fabs(b) <= DBL_MAX);
+    if (t >= ku && t < k)   // the steps after a lost vector: an error if they left the range
+        bad = !(fabs(alpha[(size_t)t * NC + vc]) <= DBL_MAX) || !(fabs(beta[(size_t)t * NC + vc]) <= DBL_MAX);
     if (__syncthreads_or(bad)) {
         if (t == 0) {
             s_all[gidx] = NAN;

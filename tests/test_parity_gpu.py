@@ -1029,33 +1029,80 @@ def test_one_sweep_step_five_wavefronts(ec, k, rule):
 
 
 @pytest.mark.parametrize("form,k", [("count", 129), ("count", 150), ("smooth", 32), ("smooth", 16), ("grad", 32),
-                                    ("batch", 130)])
-def test_lost_basis_is_reported(ec, form, k):
+                                    ("grad", 16), ("batch", 130)])
+@pytest.mark.parametrize("b", [1e-9, 1e-5])
+def test_lost_basis_ends_a_column(ec, form, k, b):
     """The forms that make one Gram-Schmidt pass a step lose the basis under
-    couplings of 1e-9 of the norm (alpha off by 2 and far more): an error, not
-    those numbers.  Moderate couplings (1e-5) are answered as ever."""
+    couplings of 1e-9 of the norm (alpha off by 2 and far more within 16 steps).
+    The column's result is that of the steps before the lost vector, k_used of
+    them, as if they had been asked for (coefficients that leave the range of a
+    double afterwards are an error, as they were).  Couplings of 1e-5 are answered
+    with all steps."""
     N = 160
-    for b in (1e-9, 1e-5):
-        A, v, a = weak_chain(N, b)
-        Ad, Vd = ec.upload_csr(A), torch.from_numpy(v).cuda()
-        M1 = W.PrecSpec("cheb", (N, 1, 1), 1.0, 1.0, 13.0, np.array([1.0]))   # M = 1
-        print("case lost basis", form, k, b, flush=True)
+    A, v, a = weak_chain(N, b)
+    Ad, Vd = ec.upload_csr(A), torch.from_numpy(v).cuda()
+    M1 = W.PrecSpec("cheb", (N, 1, 1), 1.0, 1.0, 13.0, np.array([1.0]))   # M = 1
+    none = W.PrecSpec("none")
+    xi, eta = -2.0, 1.5
+    print("case lost basis", form, k, b, flush=True)
+
+    def go(k):
         if form == "count":
-            go = lambda: ec.count(Ad, W.PrecSpec("none"), -2.0, 1.5, Vd, k)
-        elif form == "smooth":
-            go = lambda: ec.count(Ad, M1, -2.0, 1.5, Vd, k, smooth_w=0.1)
-        elif form == "grad":
-            go = lambda: ec.smooth_forward(Ad, M1, -2.0, 1.5, Vd, k, 0.1)[0]
-        else:
-            go = lambda: ec.count_batched(Ad, W.PrecSpec("none"), [N], np.array([[-2.0, 1.5]]), Vd, k)
-        if b == 1e-9:
-            with pytest.raises(ec.EcntError) as e:
-                go()
-            assert e.value.status == ec.ECNT_EDEVICE and "orthogonality" in str(e.value)
-        else:
-            r = go()
-            est = float(np.ravel(r.counts)[0]) if form == "batch" else r.estimate
-            assert abs(est - 1.0) <= 1e-8
+            return ec.count(Ad, none, xi, eta, Vd, k)
+        if form == "smooth":
+            return ec.count(Ad, M1, xi, eta, Vd, k, smooth_w=0.5)
+        if form == "grad":
+            return ec.smooth_forward(Ad, M1, xi, eta, Vd, k, 0.5, details=True)[0]
+        return ec.count_batched(Ad, none, [N], np.array([[xi, eta]]), Vd, k, details=True)
+    try:
+        r = go(k)
+    except ec.EcntError as e:
+        assert e.status == ec.ECNT_EDEVICE and b == 1e-9 and k > 128
+        return
+    ku = r.k_used.cpu().numpy().ravel()
+    s = r.per_probe.cpu().numpy().ravel()
+    if b == 1e-5:
+        assert ku.tolist() == [k, k]
+    else:
+        assert np.all(ku < 16) and np.all(ku >= 2)
+    ref = [0.0, 1.0] if form in ("count", "batch") else [0.5 * math.erfc((1.0 - xi) / 0.5), 0.5 * math.erfc((1.0 - eta) / 0.5)]
+    assert np.max(np.abs(s - ref)) <= 1e-8
+    if form in ("count", "smooth"):
+        al = r.alpha.cpu().numpy()
+        for c, t in enumerate((xi, eta)):
+            assert np.max(np.abs(al[:ku[c], c] + t - a[:ku[c]])) <= 0.1
+            assert np.all(al[ku[c]:, c] == 0.0)
+    if form == "grad" and b == 1e-9:
+        f = ec.smooth_forward(Ad, M1, xi, eta, Vd, k, 0.5)
+        dV, dx, de = ec.smooth_backward(Ad, M1, xi, eta, Vd, k, 0.5, workspace=f[1])
+        short = int(ku.min())
+        f = ec.smooth_forward(Ad, M1, xi, eta, Vd, short, 0.5)
+        dV2, dx2, de2 = ec.smooth_backward(Ad, M1, xi, eta, Vd, short, 0.5, workspace=f[1])
+        # a lost vector enters with the square of its coupling: the two shifts' columns
+        # may end at different steps
+        assert float((dV - dV2).abs().max()) <= 1e-6 and abs(dx - dx2) <= 1e-6 and abs(de - de2) <= 1e-6
+        assert abs(float(dV.sum()) + dx + de) <= 1e-6      # a common shift of A, xi and eta changes nothing
+
+
+def test_exhausted_space_is_answered(ec):
+    """A Krylov space of at most 18 dimensions asked for all of them, most of them
+    exhausted long before (the 2 x 3 x 3 Laplacian): what comes after the last
+    direction is rounding, whether or not the breakdown test sees its remainder,
+    and the estimate is the oracle's.  (The gradient's conditioning is that of
+    1 / beta; it is finite.)"""
+    dims = (2, 3, 3)
+    A = W.laplacian_csr(dims)
+    prec = W.cheb_invsqrt_prec(dims, 1.0, 2)
+    Ad = ec.upload_csr(A)
+    rng = np.random.default_rng(3)
+    for i in range(40):
+        V = W.rademacher(A.n, 48, i) * 0.1
+        xi, eta = np.sort(rng.uniform(0.5, 13.0, 2))
+        print("case exhausted", i, flush=True)
+        r, ws = ec.smooth_forward(Ad, prec, xi, eta, torch.from_numpy(V).cuda(), 18, 0.1)
+        dV = ec.smooth_backward(Ad, prec, xi, eta, torch.from_numpy(V).cuda(), 18, 0.1, workspace=ws)[0]
+        assert abs(r.estimate - oracle.count(A, prec, xi, eta, V, 18, smooth_w=0.1).estimate) <= TOL
+        assert bool(torch.isfinite(dV).all())
 
 
 def test_weak_couplings_in_fp32_storage(ec):
