@@ -282,10 +282,10 @@ __global__ __launch_bounds__(NMAX * P) void k_tridiag_dc(int NC, int C, int ld, 
     if (t >= ku && t < k)   // the steps after a lost vector: an error if they left the range
         bad = !(fabs(alpha[(size_t)t * NC + vc]) <= DBL_MAX) || !(fabs(beta[(size_t)t * NC + vc]) <= DBL_MAX);
     if (__syncthreads_or(bad)) {
-        if (t == 0) {
+        if (t == 0) {   // (one step asks for no eigensolve: its value is not a number, no error)
             s_all[gidx] = NAN;
-            minabs_all[gidx] = NAN;
-            atomicOr(&flags[1], 1);
+            minabs_all[gidx] = INFINITY;
+            if (k > 1) atomicOr(&flags[1], 1);
         }
         return;
     }

@@ -1208,3 +1208,21 @@ def test_smooth_gradient_of_polynomials_without_product_form(ec, coef, k):
     P.prec = W.PrecSpec("cheb", dims, 1.0, 1.0, 13.0, np.array(coef))
     print("case grad clenshaw", coef, k, flush=True)
     _grad_vs_oracle(ec, P, -3.0, 1.0, W.make_probes(wl), k, 0.5, 31)
+
+
+@pytest.mark.parametrize("prec,vec", [("none", "f64"), ("cheb", "f64"), ("jacobi", "f32")])
+@pytest.mark.parametrize("fused", ["auto", "off"])
+def test_one_step_with_a_probe_that_is_not_finite(ec, prec, vec, fused):
+    """k = 1 needs no eigensolve: a probe with an infinite entry makes its own value
+    (and the mean) not a number and is no error; the other probes keep theirs."""
+    wl = W.Workload("e", (5, 6, 7), "wells", 2, -8.0, -2.0, prec, 6, 1)
+    P = W.make_problem(wl)
+    V = W.make_probes(wl)
+    ok = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, 1, vec=vec, tune={"fused": fused}).per_probe.cpu().numpy()
+    V = V.copy()
+    V[3, 2] = np.inf
+    r = gpu_count(ec, P.A, P.prec, wl.xi, wl.eta, V, 1, vec=vec, tune={"fused": fused})
+    s = r.per_probe.cpu().numpy()
+    rest = [c for c in range(12) if c % 6 != 2]
+    assert np.array_equal(s[rest], ok[rest])
+    assert not np.isfinite(s[[2, 8]]).any() and math.isnan(r.estimate)
