@@ -166,14 +166,14 @@ __global__ __launch_bounds__(512) void k_sweep_fin(int C, int nseg, int rows, in
     }
     const double uu = S[0];
     const bool was = i == 0 ? uu > 0.0 : active[v] != 0;
-    const double n2 = fmax(uu - hh, 0.0), b = sqrt(n2);
+    const double n2 = uu - hh <= 0.0 ? 0.0 : uu - hh, b = sqrt(n2);   // (not a number stays one)
     // the breakdown test of k_norm_fin
     double rm = 0.0;
     bool on = was;
     if (i > 0) {
         rm = fmax(runmax[v], was ? fabs(a_last) : 0.0);
         if (i > 1) rm = fmax(rm, at(beta, i - 1));
-        on = was && b > 1e3 * eps_vec * rm;
+        on = was && !(b <= 1e3 * eps_vec * rm);
     }
     const double sg = on ? 1.0 / b : 0.0;
     const bool more = i < k;
@@ -261,9 +261,9 @@ __global__ __launch_bounds__(512) void k_arn_sweep_fin(int C, int nseg, int rows
         hh += red[0][q][lane];
         hm = fmax(hm, red[1][q][lane]);
     }
-    const double n2 = fmax(uu - hh, 0.0), b = sqrt(n2);
+    const double n2 = uu - hh <= 0.0 ? 0.0 : uu - hh, b = sqrt(n2);   // (not a number stays one)
     double rm = i > 0 ? fmax(runmax[v], hm) : 0.0;
-    const bool on = was && (i == 0 || b > 1e3 * eps_vec * rm);
+    const bool on = was && (i == 0 || !(b <= 1e3 * eps_vec * rm));
     const double sg = on ? 1.0 / b : 0.0;
     if (on && i > 0) rm = fmax(rm, b);
     const bool more = i < k;

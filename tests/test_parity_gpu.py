@@ -1226,3 +1226,24 @@ def test_one_step_with_a_probe_that_is_not_finite(ec, prec, vec, fused):
     rest = [c for c in range(12) if c % 6 != 2]
     assert np.array_equal(s[rest], ok[rest])
     assert not np.isfinite(s[[2, 8]]).any() and math.isnan(r.estimate)
+
+
+@pytest.mark.parametrize("entry", [1e300, math.inf, math.nan])
+@pytest.mark.parametrize("form,k", [("count", 2), ("count", 9), ("arnoldi", 3)])
+def test_overflow_is_an_error_not_a_breakdown(ec, entry, form, k):
+    """An entry of A whose square leaves the range of a double: |u|^2 is not finite,
+    which is no small remainder, so the count is EDEVICE and not the rule of the
+    steps before it."""
+    dims = (6, 5, 7)
+    A = W.laplacian_csr(dims)
+    val = A.val.copy()
+    val[40] = entry
+    A = W.CSR(A.n, A.row_ptr, A.col_idx, val)
+    Ad, V = ec.upload_csr(A), torch.from_numpy(W.rademacher(A.n, 4, 3)).cuda()
+    with pytest.raises(ec.EcntError) as e:
+        if form == "count":
+            ec.count(Ad, W.cheb_invsqrt_prec(dims, 1.0, 4), 2.0, 7.0, V, k)
+        else:
+            T = W.PrecSpec("cheb", dims, 1.0, 1.0, 13.0, W.cheb_interp_coeffs(lambda x: 1.0 / x, 1.0, 13.0, 8))
+            ec.count_arnoldi(Ad, T, 2.0, 7.0, V, k)
+    assert e.value.status == ec.ECNT_EDEVICE
