@@ -526,6 +526,9 @@ def batch_accuracy(r):
             "method_exact": "LDL^T Sylvester inertia (nested dissection)"}
 
 
+# The probe whose mix of reads and writes is the family's.  A probe is one kernel's
+# rate at one size, no bound: FP32 and gradient updates (c3, c5) reach 5.5 to 5.6 TB/s
+# where the update_mix probe reads 5.2.
 CEILING_KIND = {"lz_sweep": "update_mix", "lz_update": "update_mix", "bw_update": "update_mix",
                 "blk_update": "update_mix", "lz_dots": "read", "bw_dots": "read", "blk_dots": "read"}
 

@@ -476,13 +476,15 @@ static ecnt_status make_plan(Plan &p, int64_t n, int64_t m, int S, const ecnt_pr
 
 // The one-sweep step serves the plain FP64 recurrence (the differentiated form
 // keeps the coefficients of the two-read step, the FP32 form its points of
-// rounding) up to the slots that a workgroup's wavefronts can hold.  Its
+// rounding) up to kSweepMaxK steps, and holds the basis where the two-read step's
+// one Gram-Schmidt pass does not (k_dots_fin).  Its
 // partial sums take k + 2 rows a chunk, not kPartRows, and it needs k + 2 more
 // doubles per column: where k is large the chunks get longer until it takes no
 // more workspace than the two-read form, which runs where none is long enough.
-// No size was found where the two-read form is faster: whole counts of 33 k to
-// 390 k rows and 64 to 512 columns took 0.62 to 0.80 of its time, and it makes
-// as many launches per step.
+// No size was found where the two-read form is faster: whole counts took 0.62 to
+// 0.80 of its time at 33 k to 390 k rows and 64 to 512 columns, and at 210 to 10 k
+// rows and 2 to 128 columns (k = 1 to 100) the whole change to this form, the
+// eigensolves and the launches took 0.40 to 0.77; it makes as many launches per step.
 static void plan_onesweep(Plan &p, SegHost &sh)
 {
     p.onesweep = 0;

@@ -1,11 +1,12 @@
 // Quadrature kernels: batched symmetric tridiagonal eigensolve and the probe
 // average.
 //
-// Per column c (one lane each): the Lanczos matrix J_k (Section 3.1, eq. Tk),
-// or the generalized averaged matrix of Section 3.4 (eq. GA_Tk), is
-// diagonalized by implicit QR sweeps with Wilkinson shifts, accumulating only
-// the first row of the eigenvector matrix (its entries are the z_i(1) of
-// eq. gauss_quad).  Then
+// Per column c: the Lanczos matrix J_k (Section 3.1, eq. Tk), or the generalized
+// averaged matrix of Section 3.4 (eq. GA_Tk), is diagonalized by divide and
+// conquer, a workgroup per column (k_tridiag_dc), or, many columns of order 16 and
+// less, by implicit QR sweeps with Wilkinson shifts, a lane per column (k_tridiag);
+// either carries only the first row of the eigenvector matrix (its entries are
+// the z_i(1) of eq. gauss_quad).  Then
 //   s_c = |v|^2 * sum_i z_i(1)^2 h(theta_i)         (eq. gauss_quad, Algorithm 2)
 // and, over probes, the mean and sample variance of the per-probe values
 // (eq. rand_prec_quad; the interval count is the difference of two shifts).

@@ -16,9 +16,10 @@
 // of rounding (it is what the local recurrence loses in one step), so the
 // second-order terms of C Q h that are dropped lie below rounding, and
 // |r|^2 = |u_i|^2 - |h|^2 loses nothing.  alpha_i = alpha^ + h_i of the next
-// step (the part of u_{i+1} left along q_i).  The basis stays orthogonal as in
-// the two-read form: every q_i has been orthogonalized against all of q_0..
-// q_{i-1} before C q_i enters anything.
+// step (the part of u_{i+1} left along q_i).  The basis stays orthogonal: every
+// q_i has been orthogonalized against all of q_0..q_{i-1} before C q_i enters
+// anything, and u_i was small against C q_{i-1} before that pass, not after it, so
+// it also holds where the two-read form loses it (couplings below 1e-7 of the norm).
 //
 // Bound: HBM.  Step i reads i + 2 block vectors and writes 2, against 2i + 3
 // read and 1 written for dots and update.  64^3 x 512 columns, k = 30: 116 ms
